@@ -127,26 +127,29 @@ typedef struct {
 
 /* Launch parameters of the ragged batched path. Start from
  * nrm_default_batch_params(). A row's result depends on these, on its length,
- * dtypes and start alignment modulo 16 bytes, never on the other rows. */
+ * dtypes and start alignment modulo 128 bytes, never on the other rows.
+ * block, unroll, map_unroll, grid, short_regs, map_block and map_grid shape the
+ * three launches that take the longer rows when resident_segments is 0; with
+ * resident rows those rows are units of one persistent kernel. */
 typedef struct {
   int32_t block;       /* threads per block: 64..1024, multiple of 64 */
   int32_t unroll;      /* tile sums: 16-byte vectors per thread per iteration: 1, 2, 4, 8 */
   int32_t map_unroll;  /* tile divides: 16-byte vectors per thread per iteration: 1, 2, 4, 8 */
-  int32_t grid;        /* persistent blocks of the planner-fed phase 1 (sums, single-pass rows) */
-  int32_t tile_log2;   /* a long row is cut into tiles of 2^tile_log2 elements: 10..22 */
+  int32_t grid;        /* blocks of phase 1 (sums, single-pass rows) */
+  int32_t tile_log2;   /* a long row is cut into tiles of 2^tile_log2 elements: 10..22 (in the resident
+                          rows' kernel at most 2^21) */
   int32_t short_regs;  /* 16-byte vectors per thread held in registers by a single-pass row:
                           1, 2, 4 or 8; rows with n <= block * short_regs * 4 take one pass
                           (one read, one write) */
-  int32_t graph;       /* 1 (default): capture the launch sequence once per staging buffer in a
-                          hipGraph and replay it (captured on a stream of the library's own, on
-                          first use); 0: launch the kernels one by one */
+  int32_t graph;       /* 1 (default): batches of at least 2^27 elements (capacity, in the CSR forms)
+                          replay a hipGraph of the launch sequence, captured on a stream of the
+                          library's own on first use (smaller ones are launched kernel by kernel, which
+                          costs the host less than a replay); 0: every batch is launched kernel by kernel */
   int32_t map_block;   /* threads per block of the divide phase: 64..1024, multiple of 64 */
-  int32_t map_grid;    /* persistent blocks G of the divide phase: the long rows' concatenation is
-                          cut into about G * m equal chunks of at most about one tile each, so
-                          that every block divides the same number of elements */
-  int32_t keep_mib;    /* 0..4096: phase 1 reads the long rows' last tiles, up to this many MiB,
-                          with a temporal hint (the rest non-temporal), so that the divide phase
-                          finds them in the last-level cache (256 MB on MI355X) */
+  int32_t map_grid;    /* blocks of the divide phase */
+  int32_t keep_mib;    /* 0..4096: the long rows' last tiles, up to this many MiB, are summed with
+                          temporal loads (the rest non-temporal), so that their divide finds them in the
+                          last-level cache (256 MB on MI355X) */
   int32_t resident_segments; /* 0..64: a row of n <= resident_segments * 2^14 elements crosses HBM
                                 twice instead of three times: each of its segments of 2^14 elements
                                 is held in one block's registers from its read to its write while the
@@ -154,15 +157,15 @@ typedef struct {
                                 single-pass or tile path) */
   int32_t resident_grid;     /* persistent 512-thread blocks of the resident rows' kernel, 1..2^20 and
                                 at least resident_segments: a row's blocks wait for each other, so the
-                                device must be able to run that many of them at once (two per CU fit) */
+                                device must be able to run that many of them at once (two per CU fit;
+                                fewer are launched for a batch that cannot use them) */
   int32_t wave_max;          /* 0..2048: a row of 0 < n <= wave_max elements is taken by one wavefront
                                 (64 lanes), or for n <= 256 by a quarter of one (16 lanes, four such
                                 rows per wavefront at once): read into registers, summed across the
                                 lanes by DPP moves with no LDS, barrier or work claim, divided from
                                 the registers and written (two HBM transfers). 0: off (such rows take
-                                the resident or single-pass path) */
-  int32_t wave_grid;         /* 256-thread blocks of the short rows' kernel, 1..2^20; its W wavefronts
-                                take the rows statically (wavefront w: rows w, w + W, ...) */
+                                the path of the rows of up to 2^14 elements) */
+  int32_t wave_grid;         /* 1..2^20; without effect: the short rows' grid follows the batch */
 } nrm_batch_params;
 
 /* One row of a batch given as a table: `in` and `out` are device arrays of
@@ -360,8 +363,8 @@ int nrm_softmax_batched(nrm_ctx* ctx, float* out, const float* in, const int64_t
 /* Table form: `rows` is a HOST array of nrows descriptors (device data
  * pointers), staged in the context's pinned memory, which the device reads in
  * place; rows may mix dtypes. Rows are validated on the host. The context
- * keeps four such staging buffers and uses them in turn (the CSR forms stage
- * their arguments the same way): a call blocks the host only while the call
+ * keeps four such staging buffers and uses them in turn (a CSR call that
+ * replays a graph uses them too): a call blocks the host only while the call
  * four before it on the same context has not finished. */
 int nrm_normalize_rows(nrm_ctx* ctx, const nrm_row* rows, int64_t nrows, int accum, void* stream);
 
@@ -408,7 +411,7 @@ typedef struct {
 typedef struct {
   int32_t slots;             /* concurrent batches (each its own stream, workspace, graph): 1..64 */
   int32_t batching;          /* 1: one ragged batched launch per admitted group; 0: one plain call per request */
-  int32_t graph;             /* 1: batched launches replay a captured hipGraph */
+  int32_t graph;             /* 1: large batched launches replay a captured hipGraph (nrm_batch_params) */
   int32_t accum;             /* nrm_accum */
   int32_t hold_outputs;      /* 1: outputs (and their budget) stay until nrm_server_release */
   int32_t use_batch_params;  /* 1: use batch_params for the slots, else the library defaults */
@@ -424,8 +427,7 @@ typedef struct {
                                 (yielding) this long before it blocks, so that an arrival within
                                 that time is picked up without a thread wake-up */
   int32_t min_batch_rows;    /* 1..2^20: with batching, a group of fewer requests runs as one plain
-                                call per request on its slot (a small call is one launch; the batched
-                                call costs its planner and five kernels whatever the group's size) */
+                                call per request on its slot */
   int64_t budget_bytes;      /* HBM admission budget: input + output bytes of admitted requests */
   int64_t arena_bytes;       /* device arena for outputs (0: two thirds of the budget) */
   int64_t max_batch_rows;    /* requests per batch */
@@ -534,7 +536,7 @@ const char* nrm_last_error(void);
 int nrm_set_timing(nrm_ctx* ctx, int enable);
 int nrm_kernel_times(nrm_ctx* ctx, double* reduce_ms, double* map_ms, int64_t* calls);
 /* The same for batched calls: summed duration of each call's whole launch
- * sequence (staging copy, planner, both phases), and the number of calls. */
+ * sequence, and the number of calls. */
 int nrm_batch_times(nrm_ctx* ctx, double* total_ms, int64_t* calls);
 
 #ifdef __cplusplus

@@ -22,53 +22,63 @@ static_assert(sizeof(RowDesc) == sizeof(nrm_row), "RowDesc must match nrm_row");
 
 enum { BATCH_CSR = 0, BATCH_TABLE = 1 };
 
-// Per-call inputs, written by the host into pinned memory that the planner
-// reads in place, so that a captured graph replays with new contents.
+// Per-call inputs, passed as a kernel argument.
 struct BatchHeader {
   int64_t nrows;
   int32_t mode;            // BATCH_CSR or BATCH_TABLE
   int32_t csr_in_dt, csr_out_dt;
-  int32_t pad;
+  int32_t rows_per_block;  // rows each block of batch_rows_kernel takes: 1..8 or ROWS_MAX
   const int64_t* offsets;  // CSR: rows + 1 offsets (device)
   const char* csr_in;
   char* csr_out;
   int64_t capacity;        // CSR: elements addressable through csr_in / csr_out
   const RowDesc* table;    // TABLE: the row table (pinned host memory)
   float* lse;              // softmax: each row's log-sum-exp (device), or NULL
+  int64_t run_max;         // rows of wave_max < n <= run_max are run by a block of batch_rows_kernel
 };
 
-// Device error bits (OR-ed by the planner, read by nrm_get_device_error).
+// Device error bits (OR-ed by the kernels, read by nrm_get_device_error).
 enum {
   NRM_DEVERR_OFFSETS = 1,   // CSR offsets negative, decreasing or past capacity
   NRM_DEVERR_ROW = 2,       // a table row with n < 0, bad dtype, NULL pointer, or too many tiles
-  NRM_DEVERR_CAPACITY = 4,  // more rows or work items than the workspace holds
+  NRM_DEVERR_CAPACITY = 4,  // more rows or list entries than the workspace holds
   NRM_DEVERR_TARGET = 8,    // NLL loss: a target outside [0, C) that is not ignore_index
   NRM_DEVERR_STALL = 16,    // a resident row's segments did not all arrive within the spin limit
 };
 
 constexpr int64_t MAX_ROW_TILES = 65536;  // partials the per-row combine merges
 
-// One work item: a tile of a long row, or a whole short row (tile 0).
+// One entry of a work list: a tile of a long row, a segment of a resident
+// row, or a whole single-pass row (tile 0), with the row's descriptor (a
+// reader needs no second load). row -1: an empty entry.
 struct Item {
+  RowDesc d;
   int32_t row;
   int32_t tile;
 };
 
-// Counters the planner leaves for the later kernels (device memory).
+// Words the kernels of one call share (device memory, zero at first; 64-bit).
+// The counters of the work lists are in two sets, used by calls in turn, each
+// counter on a 128-byte line of its own.
+constexpr int CNT_LINE = 16;
 enum {
-  CNT_ITEMS = 0,       // all work items of phase 1
-  CNT_LONG_ITEMS = 1,  // the leading items that are tiles of long rows
-  CNT_LONG_ROWS = 2,   // long rows
-  CNT_LONG_ELEMS = 3,  // elements in long rows: the length of phase 2's range
-  CNT_CHUNK = 4,       // elements per phase-2 chunk
-  CNT_CHUNKS = 5,      // phase-2 chunks
-  CNT_LSE = 6,         // softmax: the header's lse pointer, for the kernels after the planner
-  CNT_DISPENSE = 7,    // resident units handed out so far (set to 0 by the planner)
-  CNT_EPOCH = 8,       // this call's number: tags the resident rows' published partials
-  CNT_STALL = 9,       // the number of the last call in which a resident wait gave up
-  CNT_ROWS = 10,       // the batch's rows (0 when the planner rejected the batch)
-  CNT_COUNT = 11,
+  CNT_CALL = 0,      // the last call's number
+  CNT_CALL_RUN = 1,  // the number of the call that runs, for its later launches
+  CNT_LSE = 2,       // softmax: the header's lse pointer, for the later launches
+  CNT_ORDERED = 4,   // blocks whose entries block_shorts orders (0: more than it holds)
+  CNT_STALL = 3,     // the tag of the last call in which a wait gave up
+  CNT_TAKEN = CNT_LINE,  // list entries taken so far by the resident rows' kernel
+  CNT_SET0 = 2 * CNT_LINE,
 };
+enum { LIST_TILES = 0, LIST_SHORT = 1, LIST_LONG_ROWS = 2, LIST_COUNTERS = 3 };
+constexpr int CNT_SET_STRIDE = LIST_COUNTERS * CNT_LINE;
+constexpr int CNT_COUNT = CNT_SET0 + 2 * CNT_SET_STRIDE;
+
+// The entries of `shorts` that one block of batch_rows_kernel appended.
+struct BlockShorts {
+  int64_t base, count;
+};
+constexpr int ORDERED_BLOCKS = 512;
 
 // One row's reduction result: the sum (a) for normalize, or the exponent and
 // the scaled sum (a = k, b = s) for softmax.
@@ -76,51 +86,46 @@ struct RowRes {
   float a, b;
 };
 
-// Kernel arguments: workspace pointers, fixed for a context's workspace.
+// Kernel arguments: workspace pointers, fixed for a context's workspace, and
+// the call's header (batch_rows_kernel only).
 struct BatchArgs {
-  const BatchHeader* hdr;
-  RowDesc* rows;         // resolved rows [cap_rows]
-  Item* items;           // [cap_items]: the long rows' tiles first, then the short rows
-  int64_t* lrow_first;   // [cap_rows]: first item (and partial) of each long row, in row order
-  RowDesc* lrows;        // [cap_rows]: the long rows' descriptors, in row order
-  int64_t* lstart;       // [cap_rows]: each long row's first position in the long rows' concatenation
-  RowRes* lsum;          // [cap_rows]: each long row's result (written between the phases)
-  int32_t* chunk_lrow;   // [cap_chunks]: the long row in which each phase-2 chunk starts
+  BatchHeader header;
+  Item* tiles;           // [cap_items]: the long rows' tiles
+  Item* shorts;          // [cap_items]: the resident rows' segments, or the single-pass rows
+  BlockShorts* block_shorts;  // [ORDERED_BLOCKS]
+  int64_t* lrow_first;   // [cap_rows]: the first entry of each long row (resident rows off)
   int64_t* cnt;          // [CNT_COUNT]
   int* error;            // [1]
-  void* partials;        // [cap_items] x 8 bytes
   int64_t cap_rows;
   int64_t cap_items;
-  int64_t cap_chunks;
   int64_t tile;          // elements per tile of a long row: 2^tile_log2
   int tile_log2;
-  int64_t short_max;     // rows with n <= short_max take one pass
-  int64_t map_grid;      // phase 2 blocks: the chunks are sized to a multiple of it
-  int64_t min_chunk;     // elements of one full phase-2 block-iteration: the smallest chunk
-  int64_t keep_tiles;    // phase 1 reads the last this many long-row tiles with a temporal hint
-  // resident rows (res_on): a row of n <= short_max elements is cut into
-  // segments of 2^RES_LOG2 elements, one work item each, each held in one
+  int64_t short_max;     // longer rows are long
+  int64_t keep_tiles;    // the last this many tiles are summed with temporal loads
+  // rows of 0 < n <= wave_max elements are taken by 16 lanes or one wavefront
+  // (0: none; at most WAVE_MAX_ELEMS)
+  int64_t wave_max;
+  // resident rows (res_on): a row of 2^RES_LOG2 < n <= short_max elements is
+  // cut into segments of 2^RES_LOG2 elements, one entry each, each held in one
   // block's registers from its read to its write
   int res_on;
-  unsigned long long* tagged;  // [2 * cap_items]: each segment's partial, two tagged words
-  unsigned long long* rowtot;  // [2 * cap_items]: a resident row's total at its first item, two tagged words
-  unsigned* arrivals;          // [cap_items]: a resident row's published segments at its first item (0 between calls)
-  // short rows: a row of 0 < n <= wave_max elements is taken by one
-  // wavefront of the short rows' kernel (0: none; at most WAVE_MAX_ELEMS)
-  int64_t wave_max;
-  // split planner (split_plan): a counting kernel leaves each round's counter
-  // totals here, so that the planner's blocks scan only their own round
-  int split_plan;
-  int64_t* round_agg;          // [ceil(cap_rows / PLAN_ROUND_ROWS) * 4]
-  BatchHeader* hdr_dev;        // the header, copied to device memory by the counting launch
+  // by a row's first entry: its entries' partials (two tagged words each),
+  // its total (two tagged words), and the count of its published partials (0
+  // between calls); without resident rows tile_tagged and tile_total hold
+  // plain partials and results
+  unsigned long long* tagged;       // [2 * cap_items], shorts
+  unsigned long long* rowtot;       // [2 * cap_items]
+  unsigned* arrivals;               // [cap_items]
+  unsigned long long* tile_tagged;  // [2 * cap_items], tiles
+  unsigned long long* tile_total;   // [2 * cap_items]
+  unsigned* tile_arrivals;          // [cap_items]
 };
 
-// The planner takes rows PLAN_ROUND_ROWS at a time (a "round", one block).
-// Up to PLAN_SPLIT_ROWS rows of capacity every planner block scans every
-// round itself (one launch); above, a counting launch first leaves each
-// round's totals, and each planner block scans its own round only.
-constexpr int64_t PLAN_ROUND_ROWS = 1024;
-constexpr int64_t PLAN_SPLIT_ROWS = 4096;
+// batch_rows_kernel: blocks of ROWS_BLOCK threads, at most ROWS_MAX rows each
+// (four per wavefront).
+constexpr int ROWS_BLOCK = 512;
+constexpr int ROWS_WAVES = ROWS_BLOCK / 64;
+constexpr int ROWS_MAX = 4 * ROWS_WAVES;
 
 // Elements of one resident segment: 512 threads x 8 vectors of 4 binary32
 // (4 vectors of 8 for 2-byte inputs); two blocks fit a CU's registers.
@@ -128,24 +133,26 @@ constexpr int RES_LOG2 = 14;
 constexpr int RES_BLOCK = 512;
 constexpr int RES_MAX_SEGMENTS = 64;  // one wavefront lane per segment in the merge
 
-// The short rows' kernel: blocks of WAVE_BLOCK threads, rows of at most
-// WAVE_MAX_ELEMS elements (2048 binary32: eight 16-byte vectors per lane).
-constexpr int WAVE_BLOCK = 256;
+// The longest row of one wavefront (2048 binary32: eight 16-byte vectors per lane).
 constexpr int64_t WAVE_MAX_ELEMS = 2048;
 
 struct BatchPlan {
   int acc;
+  int64_t rows_grid;  // blocks of batch_rows_kernel
+  bool lists;         // rows may be listed: launch the lists' kernels
+  int64_t res_grid;   // persistent blocks of the resident rows' kernel
+  // resident rows off: the three list kernels' shapes
   int block;
-  int unroll;       // tile reduce: vectors per thread per iteration
-  int map_unroll;   // tile map
+  int unroll;       // tile sums: vectors per thread per iteration
+  int map_unroll;   // tile divides
   int short_regs;   // vectors per thread held for a single-pass row
-  int64_t grid;     // persistent blocks of phase 1 and of the row sums
+  int64_t grid;     // blocks of phase 1 and of the row sums
   int map_block;    // phase 2
   int64_t map_grid;
-  int64_t res_grid; // persistent blocks of the resident-row kernel (0: none launched)
-  int64_t wave_grid; // blocks of the short rows' kernel (0: none launched)
 };
 
+// The first launch of a sequence, for a graph's node.
+const void* rows_kernel(int acc);
 hipError_t launch_batch(const BatchPlan& p, const BatchArgs& a, hipStream_t s);
 
 }  // namespace nrm

@@ -1,10 +1,9 @@
 // C ABI of the ragged batched path (include/nrm.h): workspace and pinned
-// staging management, host validation, the launch sequence (planner, the
-// resident rows, phase 1, row sums, phase 2) and its optional capture in a
-// hipGraph. The per-call header and row table are written to pinned,
-// coherent host memory that the planner reads in place, so a captured graph
-// replays new batches unchanged; a ring of such buffers (one graph each) lets
-// a call be enqueued while the previous ones still run.
+// staging management, host validation, the launch sequence (the rows, then
+// the lists of the longer ones) and its optional capture in a hipGraph. A row
+// table is written to pinned, coherent host memory that the first launch reads
+// in place; a ring of such buffers (one graph each) lets a call be enqueued
+// while the previous ones still run.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,14 +24,17 @@ namespace {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Staging layout: the header, then the row table from this offset.
-constexpr size_t kTableOffset = 256;
-// The planner's counters, then the device error word, in one small region.
+// The call's words and counters, then the device error word, in one region.
 constexpr size_t kErrorOffset = sizeof(int64_t) * nrm::CNT_COUNT;
-constexpr size_t kSmallBytes = 128;
-static_assert(kErrorOffset + sizeof(int) <= kSmallBytes, "counters and error word must fit");
-static_assert(sizeof(BatchHeader) <= kTableOffset, "header must fit before the table");
+constexpr size_t kSmallBytes = kErrorOffset + 128;
 int64_t align_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
+
+// Batches of at least this many elements are replayed from a captured graph
+// (parameter graph = 1); smaller ones are launched kernel by kernel. On MI355X
+// hipGraphLaunch takes 15.8 us of the host whatever the graph holds, a kernel
+// launch 1.1 us: a replay is hidden only behind a call that runs longer than
+// that on the device (2^24 binary32 elements read and written: about 21 us).
+constexpr int64_t kGraphElems = int64_t(1) << 27;
 
 nrm_batch_params default_batch_params() {
   nrm_batch_params p;
@@ -100,30 +102,27 @@ int64_t short_max_of(const nrm_batch_params& p) {
 
 bool any_graph(const BatchWorkspace& w) {
   for (const auto& per_kind : w.graph)
-    for (hipGraphExec_t g : per_kind)
-      if (g) return true;
+    for (const nrm::BatchGraph& g : per_kind)
+      if (g.exec) return true;
   return false;
 }
 
 void destroy_graph(BatchWorkspace& w) {
   for (auto& per_kind : w.graph)
-    for (hipGraphExec_t& g : per_kind) {
-      if (g) (void)hipGraphExecDestroy(g);
-      g = nullptr;
+    for (nrm::BatchGraph& g : per_kind) {
+      if (g.exec) (void)hipGraphExecDestroy(g.exec);
+      if (g.graph) (void)hipGraphDestroy(g.graph);
+      g = nrm::BatchGraph();
     }
 }
 
 // Layout of the single device allocation.
 struct Layout {
-  size_t rows, items, lrow_first, lrows, lstart, lsum, chunk_lrow, round_agg, hdr_dev, small, partials, tagged, rowtot,
-      arrivals, total;
+  size_t tiles, shorts, block_shorts, lrow_first, small, tagged, rowtot, arrivals, tile_tagged, tile_total,
+      tile_arrivals, total;
 };
 
-// Phase-2 chunks a workspace holds beyond one per item: the planner sizes the
-// chunks to a multiple of the phase-2 grid when this allows it.
-constexpr int64_t kExtraChunks = 2048;
-
-Layout layout_for(int64_t cap_rows, int64_t cap_items, int64_t cap_chunks) {
+Layout layout_for(int64_t cap_rows, int64_t cap_items) {
   Layout L;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -131,20 +130,18 @@ Layout layout_for(int64_t cap_rows, int64_t cap_items, int64_t cap_chunks) {
     off = (size_t)align_up((int64_t)(off + bytes), 256);
     return at;
   };
-  L.rows = take(sizeof(RowDesc) * cap_rows);
-  L.items = take(sizeof(nrm::Item) * cap_items);
+  L.tiles = take(sizeof(nrm::Item) * cap_items);
+  L.shorts = take(sizeof(nrm::Item) * cap_items);
+  L.block_shorts = take(sizeof(nrm::BlockShorts) * nrm::ORDERED_BLOCKS);
   L.lrow_first = take(sizeof(int64_t) * cap_rows);
-  L.lrows = take(sizeof(RowDesc) * cap_rows);
-  L.lstart = take(sizeof(int64_t) * cap_rows);
-  L.lsum = take(sizeof(nrm::RowRes) * cap_rows);
-  L.chunk_lrow = take(sizeof(int32_t) * cap_chunks);
-  L.round_agg = take(sizeof(int64_t) * 4 * (size_t)ceil_div(cap_rows, nrm::PLAN_ROUND_ROWS));
-  L.hdr_dev = take(sizeof(BatchHeader));
-  L.small = take(kSmallBytes);  // the planner's counters, then the error word
-  L.partials = take(8 * cap_items);
+  // zeroed from here on
+  L.small = take(kSmallBytes);
   L.tagged = take(16 * cap_items);
   L.rowtot = take(16 * cap_items);
   L.arrivals = take(4 * cap_items);
+  L.tile_tagged = take(16 * cap_items);
+  L.tile_total = take(16 * cap_items);
+  L.tile_arrivals = take(4 * cap_items);
   L.total = off;
   return L;
 }
@@ -154,8 +151,7 @@ int reserve(nrm_ctx* c, int64_t rows, int64_t items) {
   if (rows <= w.cap_rows && items <= w.cap_items && w.dev) return NRM_OK;
   int64_t cap_rows = std::max<int64_t>({rows, w.cap_rows, 64});
   int64_t cap_items = std::max<int64_t>({items, w.cap_items, 1024});
-  const int64_t cap_chunks = cap_items + kExtraChunks;
-  Layout L = layout_for(cap_rows, cap_items, cap_chunks);
+  Layout L = layout_for(cap_rows, cap_items);
   // the old buffers may still be in use by enqueued work
   hipError_t e = hipDeviceSynchronize();
   if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
@@ -163,10 +159,10 @@ int reserve(nrm_ctx* c, int64_t rows, int64_t items) {
   void* dev = nullptr;
   e = hipMalloc(&dev, L.total);
   if (e != hipSuccess) return fail(NRM_ENOMEM, std::string("batched workspace hipMalloc: ") + hipGetErrorString(e));
-  // Per-call header and row table: pinned, coherent host memory that the
-  // planner reads directly (no copy, no DMA latency per call).
+  // Row tables: pinned, coherent host memory that the kernels read directly
+  // (no copy, no DMA latency per call).
   void* host = nullptr;
-  const size_t staging = (size_t)align_up((int64_t)(kTableOffset + sizeof(RowDesc) * (size_t)cap_rows), 256);
+  const size_t staging = (size_t)align_up((int64_t)(sizeof(RowDesc) * (size_t)cap_rows), 256);
   e = hipHostMalloc(&host, staging * nrm::kStagingRing, hipHostMallocCoherent | hipHostMallocMapped);
   if (e != hipSuccess) {
     (void)hipFree(dev);  // already failing
@@ -182,7 +178,7 @@ int reserve(nrm_ctx* c, int64_t rows, int64_t items) {
   int err_word = 0;
   if (w.dev) {
     // keep a pending device error of the old workspace
-    e = hipMemcpy(&err_word, w.error, sizeof(int), hipMemcpyDeviceToHost);
+    e = hipMemcpy(&err_word, w.args.error, sizeof(int), hipMemcpyDeviceToHost);
     if (e != hipSuccess) {  // the old workspace stays as it was
       (void)hipFree(dev);
       (void)hipHostFree(host);
@@ -196,35 +192,29 @@ int reserve(nrm_ctx* c, int64_t rows, int64_t items) {
   w.host = host;
   w.staging = staging;
   w.next = 0;
-  for (int b = 0; b < nrm::kStagingRing; ++b) {
-    char* base = static_cast<char*>(host_dev) + staging * b;
-    w.hdr[b] = reinterpret_cast<BatchHeader*>(base);
-    w.table[b] = reinterpret_cast<RowDesc*>(base + kTableOffset);
-  }
-  w.rows = reinterpret_cast<RowDesc*>(d + L.rows);
-  w.items = reinterpret_cast<nrm::Item*>(d + L.items);
-  w.lrow_first = reinterpret_cast<int64_t*>(d + L.lrow_first);
-  w.lrows = reinterpret_cast<RowDesc*>(d + L.lrows);
-  w.lstart = reinterpret_cast<int64_t*>(d + L.lstart);
-  w.lsum = reinterpret_cast<nrm::RowRes*>(d + L.lsum);
-  w.chunk_lrow = reinterpret_cast<int32_t*>(d + L.chunk_lrow);
-  w.round_agg = reinterpret_cast<int64_t*>(d + L.round_agg);
-  w.hdr_dev = reinterpret_cast<BatchHeader*>(d + L.hdr_dev);
-  w.cnt = reinterpret_cast<int64_t*>(d + L.small);
-  w.error = reinterpret_cast<int*>(d + L.small + kErrorOffset);
-  w.partials = d + L.partials;
-  w.tagged = reinterpret_cast<unsigned long long*>(d + L.tagged);
-  w.rowtot = reinterpret_cast<unsigned long long*>(d + L.rowtot);
-  w.arrivals = reinterpret_cast<unsigned*>(d + L.arrivals);
+  for (int b = 0; b < nrm::kStagingRing; ++b)
+    w.table[b] = reinterpret_cast<RowDesc*>(static_cast<char*>(host_dev) + staging * b);
+  BatchArgs& a = w.args;
+  a.tiles = reinterpret_cast<nrm::Item*>(d + L.tiles);
+  a.shorts = reinterpret_cast<nrm::Item*>(d + L.shorts);
+  a.block_shorts = reinterpret_cast<nrm::BlockShorts*>(d + L.block_shorts);
+  a.lrow_first = reinterpret_cast<int64_t*>(d + L.lrow_first);
+  a.cnt = reinterpret_cast<int64_t*>(d + L.small);
+  a.error = reinterpret_cast<int*>(d + L.small + kErrorOffset);
+  a.tagged = reinterpret_cast<unsigned long long*>(d + L.tagged);
+  a.rowtot = reinterpret_cast<unsigned long long*>(d + L.rowtot);
+  a.arrivals = reinterpret_cast<unsigned*>(d + L.arrivals);
+  a.tile_tagged = reinterpret_cast<unsigned long long*>(d + L.tile_tagged);
+  a.tile_total = reinterpret_cast<unsigned long long*>(d + L.tile_total);
+  a.tile_arrivals = reinterpret_cast<unsigned*>(d + L.tile_arrivals);
+  a.cap_rows = cap_rows;
+  a.cap_items = cap_items;
   w.cap_rows = cap_rows;
   w.cap_items = cap_items;
-  w.cap_chunks = cap_chunks;
   for (bool& p : w.staged_pending) p = false;
-  // the counters (the call number starts at 0) and the resident rows' tags
-  e = hipMemset(d + L.small, 0, kSmallBytes);
-  // tags, totals and arrival counts: contiguous, all start at 0
-  if (e == hipSuccess) e = hipMemset(d + L.tagged, 0, L.total - L.tagged);
-  if (e == hipSuccess && err_word) e = hipMemcpy(w.error, &err_word, sizeof(int), hipMemcpyHostToDevice);
+  // the call's words and counters, the tags, totals and arrival counts
+  e = hipMemset(d + L.small, 0, L.total - L.small);
+  if (e == hipSuccess && err_word) e = hipMemcpy(a.error, &err_word, sizeof(int), hipMemcpyHostToDevice);
   if (e != hipSuccess) return hip_fail(e, "hipMemset");
   for (hipEvent_t& ev : w.staged)
     if (!ev) {
@@ -241,61 +231,50 @@ int64_t items_bound(const nrm_batch_params& p, int64_t rows, int64_t elems) {
   return rows + ceil_div(std::max<int64_t>(elems, 0), int64_t(1) << lg);
 }
 
-BatchArgs args_of(const nrm_ctx* c, int buf) {
-  const BatchWorkspace& w = c->batch;
-  BatchArgs a;
-  a.hdr = w.hdr[buf];
-  a.rows = w.rows;
-  a.items = w.items;
-  a.lrow_first = w.lrow_first;
-  a.lrows = w.lrows;
-  a.lstart = w.lstart;
-  a.lsum = w.lsum;
-  a.chunk_lrow = w.chunk_lrow;
-  a.cnt = w.cnt;
-  a.error = w.error;
-  a.partials = w.partials;
-  a.cap_rows = w.cap_rows;
-  a.cap_items = w.cap_items;
-  a.cap_chunks = w.cap_chunks;
-  a.tile = int64_t(1) << c->bparams.tile_log2;
-  a.tile_log2 = c->bparams.tile_log2;
-  a.short_max = short_max_of(c->bparams);
-  a.map_grid = c->bparams.map_grid;
-  a.min_chunk = (int64_t)c->bparams.map_block * c->bparams.map_unroll * 4;
+// The tile size the kernels use: 2^tile_log2, in the resident rows' kernel at
+// most 2^21 (its 512 threads then keep a thread's summation tree within the
+// height bound whatever the block size the parameters were checked with).
+int tile_log2_of(const nrm_batch_params& p) { return p.resident_segments > 0 ? std::min(p.tile_log2, 21) : p.tile_log2; }
+
+BatchArgs args_of(const nrm_ctx* c) {
+  BatchArgs a = c->batch.args;
+  const nrm_batch_params& p = c->bparams;
+  a.tile_log2 = tile_log2_of(p);
+  a.tile = int64_t(1) << a.tile_log2;
+  a.short_max = short_max_of(p);
   // tiles counted at 4 bytes per element: at most keep_mib MiB for any dtype
-  a.keep_tiles = ((int64_t)c->bparams.keep_mib << 20) / (a.tile * 4);
-  a.res_on = c->bparams.resident_segments > 0;
-  a.tagged = w.tagged;
-  a.rowtot = w.rowtot;
-  a.arrivals = w.arrivals;
-  a.wave_max = c->bparams.wave_max;
-  a.split_plan = w.cap_rows > nrm::PLAN_SPLIT_ROWS;
-  a.round_agg = w.round_agg;
-  a.hdr_dev = w.hdr_dev;
+  a.keep_tiles = ((int64_t)p.keep_mib << 20) / (a.tile * 4);
+  a.wave_max = p.wave_max;
+  a.res_on = p.resident_segments > 0;
   return a;
 }
 
-BatchPlan plan_of(const nrm_ctx* c, int acc) {
+// The plan of a batch of `rows` rows of at most `elems` elements, the longest
+// at most `longest`, cut up as `h` says.
+BatchPlan plan_of(const nrm_ctx* c, const BatchHeader& h, int64_t rows, int64_t elems, int64_t longest, int acc) {
+  const nrm_batch_params& q = c->bparams;
   BatchPlan p;
   p.acc = acc;
-  p.block = c->bparams.block;
-  p.unroll = c->bparams.unroll;
-  p.map_unroll = c->bparams.map_unroll;
-  p.short_regs = c->bparams.short_regs;
-  p.grid = c->bparams.grid;
-  p.map_block = c->bparams.map_block;
-  p.map_grid = c->bparams.map_grid;
-  p.res_grid = c->bparams.resident_segments > 0 ? c->bparams.resident_grid : 0;
-  p.wave_grid = c->bparams.wave_max > 0 ? c->bparams.wave_grid : 0;
+  p.rows_grid = ceil_div(rows, h.rows_per_block);
+  // no row can be longer than those run on the spot: nothing is listed
+  p.lists = longest > std::max<int64_t>(h.run_max, q.wave_max);
+  // no more blocks than a small batch can list entries: a listed row of more
+  // than 2^RES_LOG2 elements has fewer than two entries per 2^RES_LOG2 of them
+  p.res_grid = std::min<int64_t>(q.resident_grid, (h.run_max > 0 ? 0 : rows) + 2 * (elems >> nrm::RES_LOG2) + 1);
+  p.block = q.block;
+  p.unroll = q.unroll;
+  p.map_unroll = q.map_unroll;
+  p.short_regs = q.short_regs;
+  p.grid = q.grid;
+  p.map_block = q.map_block;
+  p.map_grid = q.map_grid;
   return p;
 }
 
-int capture_graph(nrm_ctx* c, int acc, int buf) {
+// Capture the sequence of a large batch; each replay sets the arguments and
+// grid of its first launch (set_rows_node).
+int capture_graph(nrm_ctx* c, const BatchPlan& p, const BatchArgs& a, nrm::BatchGraph* out) {
   BatchWorkspace& w = c->batch;
-  hipGraphExec_t& g = w.graph[acc][buf];
-  if (g) (void)hipGraphExecDestroy(g);
-  g = nullptr;
   hipError_t e;
   if (!w.capture_stream) {
     e = hipStreamCreateWithFlags(&w.capture_stream, hipStreamNonBlocking);
@@ -303,59 +282,109 @@ int capture_graph(nrm_ctx* c, int acc, int buf) {
   }
   e = hipStreamBeginCapture(w.capture_stream, hipStreamCaptureModeThreadLocal);
   if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-  hipError_t e2 = nrm::launch_batch(plan_of(c, acc), args_of(c, buf), w.capture_stream);
-  hipGraph_t graph = nullptr;
-  e = hipStreamEndCapture(w.capture_stream, &graph);
-  if (e2 != hipSuccess) return hip_fail(e2, "batched launch (capture)");
-  if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
-  e = hipGraphInstantiate(&g, graph, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(graph);
-  if (e != hipSuccess) {
-    g = nullptr;
-    return hip_fail(e, "hipGraphInstantiate");
+  hipError_t e2 = nrm::launch_batch(p, a, w.capture_stream);
+  nrm::BatchGraph g;
+  e = hipStreamEndCapture(w.capture_stream, &g.graph);
+  size_t roots = 1;
+  if (e == hipSuccess && e2 == hipSuccess) e = hipGraphGetRootNodes(g.graph, &g.rows, &roots);
+  if (e == hipSuccess && e2 == hipSuccess) e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
+  if (e != hipSuccess || e2 != hipSuccess) {
+    if (g.graph) (void)hipGraphDestroy(g.graph);  // already failing
+    return e2 != hipSuccess ? hip_fail(e2, "batched launch (capture)") : hip_fail(e, "capturing the batched launches");
   }
+  *out = g;
   return NRM_OK;
 }
 
-// Stage the header (and table) in the next ring buffer, then run the launch
-// sequence on `s`.
-int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nrows, int acc,
-              hipStream_t s) {
+hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs a) {
+  void* args[] = {&a};
+  hipKernelNodeParams k;
+  std::memset(&k, 0, sizeof(k));
+  k.func = const_cast<void*>(nrm::rows_kernel(p.acc));
+  k.gridDim = dim3((unsigned)p.rows_grid);
+  k.blockDim = dim3(nrm::ROWS_BLOCK);
+  k.kernelParams = args;
+  return hipGraphExecKernelNodeSetParams(g.exec, g.rows, &k);
+}
+
+// How batch_rows_kernel is cut up; the results are the same. A wavefront costs
+// the dispatcher about 0.4 ns, so many short rows go four to a wavefront (2^20
+// rows of 64 binary32: 159 us with 32 rows per block, 489 us with 8). Rows of
+// several hundred elements take a wavefront each, one after the other: 8 per
+// block (2^18 x 1000: 350 us, with 32 377 us; 65536 x 3000: 4 per block 293 us,
+// 8 303 us). Rows run by the block take turns in it, so long ones get a block
+// (nearly) each: 16384 x 10000 in 237 us with 2 per block, 257 us with 4, and
+// 4 log-uniform up to 65536 in 288 and 280 us; and a batch of few rows one
+// block per row. Where most of the elements are in rows of more than
+// 2^RES_LOG2, which are listed anyway, so are those of wave_max < n <=
+// 2^RES_LOG2 (4096 rows up to 2^20: 614 us listed, 631 us run by their blocks).
+void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeader* h) {
+  const int64_t mean = elems / rows;
+  const int64_t block_max = p.resident_segments > 0 ? int64_t(1) << nrm::RES_LOG2 : 0;
+  h->run_max = block_max;
+  if (rows <= 512) {
+    h->rows_per_block = 1;
+  } else if (mean >= 2 * block_max) {
+    h->rows_per_block = nrm::ROWS_WAVES;
+    h->run_max = 0;
+  } else {
+    h->rows_per_block = mean >= 4096 ? 2 : mean >= 1536 ? 4 : mean > 512 || rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
+  }
+}
+
+// Run the launch sequence on `s` for a batch of at most `elems` elements whose
+// longest row has at most `longest`. A row table is staged in the next ring
+// buffer first.
+int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nrows, int64_t elems, int64_t longest,
+              int acc, hipStream_t s) {
   BatchWorkspace& w = c->batch;
   hipError_t e;
+  BatchArgs a = args_of(c);
+  a.header = h;
+  cut_rows(c->bparams, nrows, elems, &a.header);
+  BatchPlan p = plan_of(c, a.header, nrows, elems, longest, acc);
+  const bool replay = c->bparams.graph && elems >= kGraphElems;
+  const bool ring = replay || table;
   const int buf = w.next;
-  if (w.staged_pending[buf]) {  // the call that used this buffer before must be done with it
+  if (ring && w.staged_pending[buf]) {  // the call that used this buffer or graph before must be done with it
     e = hipEventSynchronize(w.staged[buf]);
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
     w.staged_pending[buf] = false;
   }
-  BatchHeader hd = h;
-  hd.table = w.table[buf];
-  char* host = static_cast<char*>(w.host) + w.staging * buf;
-  std::memcpy(host, &hd, sizeof(hd));
-  if (table) std::memcpy(host + kTableOffset, table, sizeof(RowDesc) * (size_t)nrows);
+  if (table) {
+    std::memcpy(static_cast<char*>(w.host) + w.staging * buf, table, sizeof(RowDesc) * (size_t)nrows);
+    a.header.table = w.table[buf];
+  }
   hipEvent_t* ev = nullptr;
   if (c->timing) {
     ev = &w.events[2 * (w.timed_calls % nrm::kTimingRing)];
     w.timed_calls++;
     (void)hipEventRecord(ev[0], s);  // timing only
   }
-  if (c->bparams.graph) {
-    if (!w.graph[acc][buf]) {
-      int st = capture_graph(c, acc, buf);
+  if (replay) {
+    // the sequence of any large batch: all launches, the lists' at full size
+    p.lists = true;
+    p.res_grid = c->bparams.resident_grid;
+    nrm::BatchGraph& g = w.graph[acc][buf];
+    if (!g.exec) {
+      int st = capture_graph(c, p, a, &g);
       if (st != NRM_OK) return st;
     }
-    e = hipGraphLaunch(w.graph[acc][buf], s);
+    e = set_rows_node(g, p, a);
+    if (e != hipSuccess) return hip_fail(e, "hipGraphExecKernelNodeSetParams");
+    e = hipGraphLaunch(g.exec, s);
     if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
   } else {
-    e = nrm::launch_batch(plan_of(c, acc), args_of(c, buf), s);
+    e = nrm::launch_batch(p, a, s);
     if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
   }
   if (ev) (void)hipEventRecord(ev[1], s);
-  e = hipEventRecord(w.staged[buf], s);
-  if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
-  w.staged_pending[buf] = true;
-  w.next = (buf + 1) % nrm::kStagingRing;
+  if (ring) {
+    e = hipEventRecord(w.staged[buf], s);
+    if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
+    w.staged_pending[buf] = true;
+    w.next = (buf + 1) % nrm::kStagingRing;
+  }
   return NRM_OK;
 }
 
@@ -499,7 +528,7 @@ int run_csr(nrm_ctx* c, void* out, int out_dtype, const void* in, int in_dtype, 
   h.csr_out = static_cast<char*>(out);
   h.capacity = capacity;
   h.lse = lse;
-  return run_batch(c, h, nullptr, rows, acc, s);
+  return run_batch(c, h, nullptr, rows, capacity, capacity, acc, s);
 }
 }  // namespace
 
@@ -547,7 +576,7 @@ int nrm_normalize_rows(nrm_ctx* c, const nrm_row* rows, int64_t nrows, int accum
     if (st != NRM_OK) return st;
   }
   nrm::CtxLock lk(c->mu);
-  if (longest > (int64_t(1) << c->bparams.tile_log2) * nrm::MAX_ROW_TILES)
+  if (longest > (int64_t(1) << tile_log2_of(c->bparams)) * nrm::MAX_ROW_TILES)
     return fail(NRM_EINVAL, "row too long for the batched path's tile size");
   DeviceGuard g(c->device);
   int st = reserve(c, nrows, items_bound(c->bparams, nrows, total));
@@ -556,7 +585,7 @@ int nrm_normalize_rows(nrm_ctx* c, const nrm_row* rows, int64_t nrows, int accum
   std::memset(&h, 0, sizeof(h));
   h.nrows = nrows;
   h.mode = nrm::BATCH_TABLE;
-  return run_batch(c, h, rows, nrows, accum, static_cast<hipStream_t>(stream));
+  return run_batch(c, h, rows, nrows, total, longest, accum, static_cast<hipStream_t>(stream));
 }
 
 int nrm_get_device_error(nrm_ctx* c, void* stream) {
@@ -570,7 +599,7 @@ int nrm_get_device_error(nrm_ctx* c, void* stream) {
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
   // the batched workspace's word and the context's word of the other kernels
   int word = 0;
-  for (int* p : {c->batch.dev ? c->batch.error : nullptr, c->dev_error}) {
+  for (int* p : {c->batch.dev ? c->batch.args.error : nullptr, c->dev_error}) {
     if (!p) continue;
     int w = 0;
     e = hipMemcpy(&w, p, sizeof(int), hipMemcpyDeviceToHost);
@@ -584,7 +613,11 @@ int nrm_get_device_error(nrm_ctx* c, void* stream) {
   if (!word) return NRM_OK;
   if (word & nrm::NRM_DEVERR_STALL) {
     // a wait that gave up may have left arrival counts behind: start them over
-    if (c->batch.dev) e = hipMemset(c->batch.arrivals, 0, sizeof(unsigned) * (size_t)c->batch.cap_items);
+    if (c->batch.dev) {
+      e = hipMemset(c->batch.args.arrivals, 0, sizeof(unsigned) * (size_t)c->batch.cap_items);
+      if (e == hipSuccess)
+        e = hipMemset(c->batch.args.tile_arrivals, 0, sizeof(unsigned) * (size_t)c->batch.cap_items);
+    }
     if (e == hipSuccess) e = hipMemset(c->res.arrivals, 0, sizeof(unsigned));
     if (e != hipSuccess) return hip_fail(e, "clearing the arrival counts");
   }

@@ -49,38 +49,28 @@ class DeviceGuard {
 };
 
 
+// A captured launch sequence and its first node, whose arguments each replay sets.
+struct BatchGraph {
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+  hipGraphNode_t rows = nullptr;
+};
+
 // Device workspace and host staging of the batched path.
 struct BatchWorkspace {
   int64_t cap_rows = 0;
   int64_t cap_items = 0;
-  int64_t cap_chunks = 0;
   void* dev = nullptr;         // one allocation, carved into the pointers below
-  BatchHeader* hdr[kStagingRing] = {};  // device views of the staging buffers' headers
-  RowDesc* table[kStagingRing] = {};    // device views of their row tables
-  RowDesc* rows = nullptr;
-  Item* items = nullptr;
-  int64_t* lrow_first = nullptr;
-  RowDesc* lrows = nullptr;
-  int64_t* lstart = nullptr;
-  RowRes* lsum = nullptr;
-  int32_t* chunk_lrow = nullptr;
-  int64_t* round_agg = nullptr;
-  BatchHeader* hdr_dev = nullptr;
-  int64_t* cnt = nullptr;
-  int* error = nullptr;
-  void* partials = nullptr;
-  unsigned long long* tagged = nullptr;  // resident rows' tagged partials
-  unsigned long long* rowtot = nullptr;  // resident rows' tagged totals
-  unsigned* arrivals = nullptr;          // resident rows' arrival counts
-  void* host = nullptr;        // pinned staging (host view): kStagingRing buffers of `staging` bytes,
-                               // each a header, then a row table
+  RowDesc* table[kStagingRing] = {};  // device views of the staging buffers
+  BatchArgs args{};            // the workspace's pointers and capacities
+  void* host = nullptr;        // pinned staging (host view): kStagingRing row tables of `staging` bytes
   size_t staging = 0;
-  int next = 0;                // the buffer the next call uses
+  int next = 0;                // the buffer (and graph) the next call uses
   hipEvent_t staged[kStagingRing] = {};  // recorded after the call that used the buffer
   bool staged_pending[kStagingRing] = {};
   // captured launch sequences: per reduction kind (plain, compensated,
-  // softmax) and staging buffer (the planner reads its buffer's header)
-  hipGraphExec_t graph[3][kStagingRing] = {};
+  // softmax) and staging buffer (one is not changed while its last replay runs)
+  BatchGraph graph[3][kStagingRing] = {};
   hipStream_t capture_stream = nullptr;
   // timing ring of (before, after) event pairs
   std::vector<hipEvent_t> events;

@@ -92,8 +92,14 @@ __device__ __forceinline__ u32 pack2(float a, float b) {
   }
 }
 
+template <bool NT, typename T>
+__device__ __forceinline__ void store_bits(T v, T* p) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
 // Store VEC quotients as element group `vi` of the output (VEC * size bytes).
-template <int DTO, int VEC>
+template <int DTO, int VEC, bool NT = true>
 __device__ __forceinline__ void store_vec(char* out, int64_t vi, const float (&q)[VEC]) {
   if constexpr (DTO == NRM_F32) {
     u4* p = reinterpret_cast<u4*>(out) + vi * (VEC / 4);
@@ -101,15 +107,15 @@ __device__ __forceinline__ void store_vec(char* out, int64_t vi, const float (&q
     for (int h = 0; h < VEC / 4; ++h) {
       u4 v = {bits_f32(q[4 * h]), bits_f32(q[4 * h + 1]), bits_f32(q[4 * h + 2]),
               bits_f32(q[4 * h + 3])};
-      __builtin_nontemporal_store(v, p + h);
+      store_bits<NT>(v, p + h);
     }
   } else if constexpr (VEC == 8) {
     u4 v = {pack2<DTO>(q[0], q[1]), pack2<DTO>(q[2], q[3]), pack2<DTO>(q[4], q[5]),
             pack2<DTO>(q[6], q[7])};
-    __builtin_nontemporal_store(v, reinterpret_cast<u4*>(out) + vi);
+    store_bits<NT>(v, reinterpret_cast<u4*>(out) + vi);
   } else {
     u2 v = {pack2<DTO>(q[0], q[1]), pack2<DTO>(q[2], q[3])};
-    __builtin_nontemporal_store(v, reinterpret_cast<u2*>(out) + vi);
+    store_bits<NT>(v, reinterpret_cast<u2*>(out) + vi);
   }
 }
 

@@ -484,7 +484,7 @@ __device__ __forceinline__ bool dq_long_unit(const RowDesc& d, int64_t part, int
     }
     return false;
   }
-  if (t == 0) *s_bcast = RowMap<ACC>::of(wait_total<ACC>(x)).result();
+  if (t == 0) *s_bcast = RowMap<ACC>::of(wait_tagged<ACC>(x, x.total)).result();
   lds_barrier();
   dispatch_part_map<ACC>(d, part - m, RowMap<ACC>::of(*s_bcast));
   return true;

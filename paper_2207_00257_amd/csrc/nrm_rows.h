@@ -26,20 +26,23 @@ using namespace dev;
 // after the last whole vector are handled one element per thread.
 constexpr int BODY_ALIGN = 128;
 
+// A segment has fewer than 2^31 elements (a tile, at most 2^22, is the longest),
+// so everything inside it is indexed in 32 bits: 64-bit indexes cost the
+// resident rows' kernel its registers.
 struct Geom {
-  int64_t head;        // elements before the body's 128-byte boundary
-  int64_t nvec;        // whole 16-byte vectors in the body
-  int64_t tail_begin;  // first element after the vectors
+  int head;        // elements before the body's 128-byte boundary
+  int nvec;        // whole 16-byte vectors in the body
+  int tail_begin;  // first element after the vectors
 };
 
 template <int DT>
-__device__ __forceinline__ Geom geometry(const char* p, int64_t n) {
+__device__ __forceinline__ Geom geometry(const char* p, int n) {
   constexpr int SI = Elem<DT>::SIZE, VEC = Elem<DT>::VEC;
   Geom g;
-  const int64_t mis = (int64_t)(reinterpret_cast<uintptr_t>(p) & (BODY_ALIGN - 1));
+  const int mis = (int)(reinterpret_cast<uintptr_t>(p) & (BODY_ALIGN - 1));
   g.head = mis ? (BODY_ALIGN - mis) / SI : 0;
   if (g.head > n) g.head = n;
-  g.nvec = (n - g.head) / VEC;
+  g.nvec = (int)((unsigned)(n - g.head) / VEC);
   g.tail_begin = g.head + g.nvec * VEC;
   return g;
 }
@@ -47,18 +50,18 @@ __device__ __forceinline__ Geom geometry(const char* p, int64_t n) {
 // Output vectors can be stored whole when the output segment has the same
 // alignment as the input's vector body.
 template <int DTI, int DTO>
-__device__ __forceinline__ bool out_vector_ok(const char* out_seg, int64_t head) {
+__device__ __forceinline__ bool out_vector_ok(const char* out_seg, int head) {
   constexpr int SO = Elem<DTO>::SIZE, VEC = Elem<DTI>::VEC;
   constexpr int A = VEC * SO < 16 ? VEC * SO : 16;
   return (reinterpret_cast<uintptr_t>(out_seg + head * SO) % A) == 0;
 }
 
-template <int DTI, int DTO>
-__device__ __forceinline__ void store_quotients(char* out_seg, int64_t head, int64_t v, bool vec_ok,
+template <int DTI, int DTO, bool NT = true>
+__device__ __forceinline__ void store_quotients(char* out_seg, int head, int v, bool vec_ok,
                                                 const float (&q)[Elem<DTI>::VEC]) {
   constexpr int VEC = Elem<DTI>::VEC;
   if (vec_ok) {
-    store_vec<DTO, VEC>(out_seg + head * Elem<DTO>::SIZE, v, q);
+    store_vec<DTO, VEC, NT>(out_seg + head * Elem<DTO>::SIZE, v, q);
   } else {
 #pragma unroll
     for (int c = 0; c < VEC; ++c) store_one<DTO>(out_seg, head + v * VEC + c, q[c]);
@@ -118,13 +121,13 @@ __device__ __forceinline__ void raise_shared(Acc<ACC_SOFTMAX> (&acc)[NA], float 
 // raise (raise_shared), then per element a fused multiply-add, an exp2 and an
 // addition.
 template <int DTI, int NA, int KB>
-__device__ __forceinline__ void softmax_add_held(Acc<ACC_SOFTMAX> (&acc)[NA], const u4 (&r)[KB], int64_t first,
-                                                 int64_t stride, int64_t nvec) {
+__device__ __forceinline__ void softmax_add_held(Acc<ACC_SOFTMAX> (&acc)[NA], const u4 (&r)[KB], int first,
+                                                 int stride, int nvec) {
   constexpr int VEC = Elem<DTI>::VEC;
   float m = -3.0e38f;
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
-    if (first + (int64_t)k * stride < nvec) {
+    if (first + k * stride < nvec) {
       float x[VEC];
       widen<DTI>(r[k], x);
 #pragma unroll
@@ -135,7 +138,7 @@ __device__ __forceinline__ void softmax_add_held(Acc<ACC_SOFTMAX> (&acc)[NA], co
   const float nk = -acc[0].k;
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
-    if (first + (int64_t)k * stride < nvec) {
+    if (first + k * stride < nvec) {
       float x[VEC];
       widen<DTI>(r[k], x);
 #pragma unroll
@@ -152,7 +155,7 @@ __device__ __forceinline__ void softmax_add_held(Acc<ACC_SOFTMAX> (&acc)[NA], co
 // them in a fixed order (the same in every block of the row, so that every
 // block divides by the same bits) and divides its segment from registers.
 //
-// Progress: blocks take items from a counter (CNT_DISPENSE) in item order, a
+// Progress: blocks take items from a counter in item order, a
 // row's items are consecutive, a block takes an item only once it has
 // finished the previous one, and it publishes its sum before it waits. Every row
 // before the one holding the last item taken therefore has all its items in
@@ -236,15 +239,15 @@ __device__ __forceinline__ bool given_up(const ResExchange& x, uint32_t spin) {
   return (spin & 255) == 255 && __hip_atomic_load(x.stall, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == x.ep;
 }
 
-// One thread: wait for the row's total (bounded), and return it.
+// One thread: wait for the tagged value at `words` (bounded), and return it.
 template <int ACC>
-__device__ __forceinline__ Acc<ACC> wait_total(const ResExchange& x) {
+__device__ __forceinline__ Acc<ACC> wait_tagged(const ResExchange& x, const unsigned long long* words) {
   float f[2] = {0.0f, 0.0f};
   for (uint32_t spin = 0;; ++spin) {
     bool ok = true;
 #pragma unroll
     for (int w = 0; w < Tagged<ACC>::WORDS; ++w) {
-      const unsigned long long v = __hip_atomic_load(x.total + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned long long v = __hip_atomic_load(words + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       f[w] = f32_bits((uint32_t)v);
       ok = ok && (uint32_t)(v >> 32) == x.ep;
     }
@@ -322,8 +325,8 @@ __device__ __forceinline__ Acc<ACC> gather_row(const ResExchange& x, int nseg) {
 // the lowest latency for a single row of few segments) instead of waiting for
 // the last arrival's total (fewer polls: the better throughput for a batch);
 // the arrival count then only finds the last block, which moves the call
-// number on.
-template <int DTI, int DTO, int ACC, int BLOCK, int LOG2, int PER_LANE, bool DIRECT = false>
+// number on. ALONE: the row is this one segment (no exchange is compiled in).
+template <int DTI, int DTO, int ACC, int BLOCK, int LOG2, int PER_LANE, bool DIRECT = false, bool ALONE = false>
 __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const ResExchange& x, Acc<ACC>* slots,
                                               RowRes* s_bcast, float* lse_row) {
   constexpr int VEC = Elem<DTI>::VEC;
@@ -333,21 +336,21 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
   constexpr int NA_MAX = ACC == NRM_ACC_F32 ? 8 : 4;
   constexpr int NA = KB * VEC < NA_MAX ? KB * VEC : NA_MAX;
   const int t = threadIdx.x;
-  const int64_t S = int64_t(1) << LOG2;
+  constexpr int S = 1 << LOG2;
   const int64_t b = (int64_t)seg << LOG2;
-  const int64_t n = d.n - b < S ? d.n - b : S;
+  const int n = d.n - b < S ? (int)(d.n - b) : S;
   const int nseg = (int)((d.n + S - 1) >> LOG2);
   const char* in_seg = d.in + b * Elem<DTI>::SIZE;
   char* out_seg = d.out + b * Elem<DTO>::SIZE;
   const Geom g = geometry<DTI>(in_seg, n);
   const u4* body = reinterpret_cast<const u4*>(in_seg + g.head * Elem<DTI>::SIZE);
   const bool has_head = t < g.head;
-  const int64_t ti = g.tail_begin + t;
+  const int ti = g.tail_begin + t;
   const bool has_tail = ti < n;
   u4 r[KB];
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
-    const int64_t v = t + (int64_t)k * BLOCK;
+    const int v = t + k * BLOCK;
     if (v < g.nvec) r[k] = load_vec<true>(body + v);
   }
   const float xh = has_head ? load_one<DTI>(in_seg, t) : 0.0f;
@@ -360,7 +363,7 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
   } else {
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      if (t + (int64_t)k * BLOCK < g.nvec) {
+      if (t + k * BLOCK < g.nvec) {
         float xv[VEC];
         widen<DTI>(r[k], xv);
 #pragma unroll
@@ -372,7 +375,7 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
   if (has_tail) acc[0].add(xt);
   merge_chains<ACC, NA>(acc);
   const Acc<ACC> tot = block_reduce<ACC>(acc[0], slots);
-  if (nseg == 1) {
+  if (ALONE || nseg == 1) {
     if (t == 0) {
       const RowMap<ACC> f0 = RowMap<ACC>::of(tot);
       *s_bcast = f0.result();
@@ -413,7 +416,7 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
         if (x.call) __hip_atomic_fetch_add(x.call, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     } else if (t == 0) {
-      total = wait_total<ACC>(x);
+      total = wait_tagged<ACC>(x, x.total);
     }
     if (t == 0) {
       const RowMap<ACC> f0 = RowMap<ACC>::of(total);
@@ -428,7 +431,7 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
   const bool vec_ok = out_vector_ok<DTI, DTO>(out_seg, g.head);
 #pragma unroll
   for (int k = 0; k < KB; ++k) {
-    const int64_t v = t + (int64_t)k * BLOCK;
+    const int v = t + k * BLOCK;
     if (v < g.nvec) {
       float xv[VEC], q[VEC];
       widen<DTI>(r[k], xv);
@@ -441,13 +444,13 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
   if (has_tail) store_one<DTO>(out_seg, ti, f(xt));
 }
 
-template <int ACC>
+template <int ACC, bool ALONE = false>
 __device__ __forceinline__ void dispatch_resident(const RowDesc& d, int seg, const ResExchange& x, Acc<ACC>* slots,
                                                   RowRes* s_bcast, float* lse_row) {
   if constexpr (ACC == ACC_SOFTMAX) {
-    resident_unit<NRM_F32, NRM_F32, ACC, RES_BLOCK, RES_LOG2, 1>(d, seg, x, slots, s_bcast, lse_row);
+    resident_unit<NRM_F32, NRM_F32, ACC, RES_BLOCK, RES_LOG2, 1, false, ALONE>(d, seg, x, slots, s_bcast, lse_row);
   } else {
-#define NRM_RU(I, O) return resident_unit<I, O, ACC, RES_BLOCK, RES_LOG2, 1>(d, seg, x, slots, s_bcast, lse_row)
+#define NRM_RU(I, O) return resident_unit<I, O, ACC, RES_BLOCK, RES_LOG2, 1, false, ALONE>(d, seg, x, slots, s_bcast, lse_row)
     switch (d.in_dt * 3 + d.out_dt) {
       case NRM_F32 * 3 + NRM_F32: NRM_RU(NRM_F32, NRM_F32);
       case NRM_F32 * 3 + NRM_BF16: NRM_RU(NRM_F32, NRM_BF16);
