@@ -117,12 +117,12 @@ typedef struct {
                            per thread), reduces it, and divides from the registers: one read,
                            one write, one launch. Default 0 (never): the resident form below was
                            faster per call at every size */
-  int32_t resident_n;   /* 0..2^20: n in (small_n, resident_n] runs as one launch of one 256-thread
-                           block per 4096 elements, each block holding its elements in registers
-                           while the blocks exchange their sums: one read, one write, one launch
-                           (all n / 4096 blocks must be able to run at once: one per CU). Up to 64
-                           blocks every block reads every block's sum; beyond, the last block to
-                           arrive publishes the total. Default 2^18; 0: never */
+  int32_t resident_n;   /* 0..2^20: n in (small_n, resident_n] (compensated: at most 2^19) runs as one
+                           launch, each block holding its elements in registers while the blocks
+                           exchange their sums: one read, one write, one launch. One block of 256
+                           threads per 2^12 elements up to 2^18, above one of 512 threads per 2^14 (at
+                           most 64 blocks, all of which must be able to run at once); every block
+                           reads every block's sum. Default 2^20; 0: never */
 } nrm_params;
 
 /* Launch parameters of the ragged batched path. Start from

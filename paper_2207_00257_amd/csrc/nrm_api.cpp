@@ -57,14 +57,13 @@ nrm_params default_params() {
   p.reduce_keep_mib = 256;
   p.tile_log2 = 12;
   p.fused_combine = 1;
-  // n <= 2^18 in one launch of a block per 4096 elements (one read, one
-  // write); above, the two kernels. Measured per call on MI355X (device time
-  // of a synchronized call): 8.6-12.6 us up to 2^18 against 12.1-13.2 us for
-  // two kernels; beyond 64 segments the exchange costs more than the kernel
-  // boundary (2^20: 17.5 against 13.3 us). The one-block form (small_n) lost
-  // to it from 2^14 on (2^16: 17.5 us).
+  // n <= 2^20 in one launch of at most 64 blocks holding their elements (one
+  // read, one write); above, the two kernels. Measured per call on MI355X, back
+  // to back: 6.1 us at 2^18 and 7.2 us at 2^20 against 8.1-8.4 us for two
+  // kernels. The one-block form (small_n) loses to it from 2^14 on (2^16: 11.1
+  // against 5.2 us).
   p.small_n = 0;
-  p.resident_n = 1 << 18;
+  p.resident_n = 1 << 20;
   return p;
 }
 
@@ -91,9 +90,9 @@ int check_params(const nrm_params& p) {
 
 // The context's small workspace: the ticket (0), the sum (128), the device
 // error word (192), the mid-size single-launch form's call number (256),
-// arrival count (264), stall marker (272) and merged total (288), and from
-// 512 its segments' tagged partials (256 x 16 bytes).
-constexpr size_t kSmallWs = 512 + 256 * 16;
+// arrival count (264) and stall marker (272), and from 512 its segments'
+// tagged partials (64 x 16 bytes).
+constexpr size_t kSmallWs = 512 + 64 * 16;
 
 std::mutex g_default_mu;
 std::map<int, nrm_ctx*> g_default;
@@ -409,8 +408,7 @@ int nrm_create(nrm_ctx** ctx, int device) {
   c->ticket = reinterpret_cast<unsigned*>(sm);
   c->sum = reinterpret_cast<float*>(sm + 128);
   c->dev_error = reinterpret_cast<int*>(sm + 192);
-  c->res = nrm::PlainResidentWs{reinterpret_cast<unsigned long long*>(sm + 512),
-                                reinterpret_cast<unsigned long long*>(sm + 288), reinterpret_cast<unsigned*>(sm + 264),
+  c->res = nrm::PlainResidentWs{reinterpret_cast<unsigned long long*>(sm + 512), reinterpret_cast<unsigned*>(sm + 264),
                                 reinterpret_cast<unsigned long long*>(sm + 256),
                                 reinterpret_cast<unsigned long long*>(sm + 272), c->dev_error, c->sum};
   int st = ensure_partials(c, 16384);
@@ -556,7 +554,7 @@ int nrm_normalize_ex(nrm_ctx* c, void* out, int out_dtype, const void* in, int i
     }
     return NRM_OK;
   }
-  if (n <= q.resident_n && n <= nrm::plain_resident_capacity()) {
+  if (n <= q.resident_n && n <= nrm::plain_resident_capacity(accum)) {
     // one block per segment, held in registers across the exchange of sums
     DeviceGuard g(c->device);
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -1083,41 +1083,47 @@ hipError_t small_acc(const RowDesc& d, float* sum_out, hipStream_t s) {
 }
 
 // ---- the plain path's single-launch form for mid-size n ---------------------------------
-// n in (small_n, 2^20]: one block of PRES_BLOCK threads per segment of
-// 2^PRES_LOG2 elements (at most PRES_MAX_SEGMENTS blocks), each held in
-// registers from its read to its write while the blocks exchange their
-// segment sums as the resident rows of a batch do: two transfers and one
-// launch instead of three transfers and two launches. The grid is the
-// row's segments, so every block of the launch must be able to run at once
-// (256 blocks of 256 threads: one per CU on MI355X). The call number that
-// tags the partials lives in the workspace; the last block to arrive moves
-// it on (every block read it before arriving), so consecutive calls on one
-// workspace never read each other's partials.
+// n in (small_n, 2^20]: one block per segment of the input, at most
+// PRES_MAX_SEGMENTS of them, each held in registers from its read to its write
+// while the blocks exchange their segment sums: every block reads every sum
+// (DIRECT; one lane of a wavefront per segment). Two transfers and one launch
+// instead of three and two. The grid is the row's segments, so every block of
+// the launch must be able to run at once. The call number that tags the
+// partials lives in the workspace; the last block to arrive moves it on (every
+// block read it before arriving), so consecutive calls on one workspace never
+// read each other's partials.
+//
+// Launch and exchange latency bound it. A short input takes segments of 2^12
+// elements on 256 threads (more CUs load at once), one of more than
+// PRES_SHORT_MAX segments of 2^14 on 512, which keeps the sums of 2^20
+// elements within one wavefront's lanes and the launch within 64 blocks.
+// Per call back to back, one box: 2^18 binary32 6.1 us either way; 2^19 6.5 us
+// and 2^20 7.2 us against 8.1 and 8.4 us for the two kernels (with 256 segments
+// of 2^12 and the last block publishing the total, 8.6 and 10.9 us). The
+// compensated sum's longer chains lose that from 2^20 on (8.2 against 7.7 us;
+// 2^19: 7.5 and 7.7), so it stops at 2^19.
 constexpr int PRES_BLOCK = 256;
 constexpr int PRES_LOG2 = 12;
-constexpr int PRES_MAX_SEGMENTS = 256;
+constexpr int PRES_MAX_SEGMENTS = 64;
+constexpr int64_t PRES_SHORT_MAX = (int64_t)PRES_MAX_SEGMENTS << PRES_LOG2;
 
-template <int DTI, int DTO, int ACC, bool DIRECT>
-__global__ void __launch_bounds__(PRES_BLOCK) plain_resident_kernel(RowDesc d, PlainResidentWs w) {
+template <int DTI, int DTO, int ACC, int BLOCK, int LOG2>
+__global__ void __launch_bounds__(BLOCK) plain_resident_kernel(RowDesc d, PlainResidentWs w) {
   __shared__ Acc<ACC> slots[MAX_WAVES];
   __shared__ RowRes s_bcast;
   // the tag is never 0, the value of a slot that was never written; the last
   // block to arrive moves the call number on once every block has read it
   const unsigned long long call = __hip_atomic_load(w.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const ResExchange x{w.slots, w.total, w.arrivals, (uint32_t)(call % 0xFFFFFFFFull) + 1u, w.error, w.stall, w.call};
-  resident_unit<DTI, DTO, ACC, PRES_BLOCK, PRES_LOG2, DIRECT ? 1 : PRES_MAX_SEGMENTS / 64, DIRECT>(
-      d, blockIdx.x, x, slots, &s_bcast, nullptr);
+  const ResExchange x{w.slots, nullptr, w.arrivals, (uint32_t)(call % 0xFFFFFFFFull) + 1u, w.error, w.stall, w.call};
+  resident_unit<DTI, DTO, ACC, BLOCK, LOG2, 1, true>(d, blockIdx.x, x, slots, &s_bcast, nullptr);
   if (threadIdx.x == 0 && blockIdx.x == 0) w.sum_out[0] = s_bcast.a;  // the invariant, for nrm_get_last_sum
 }
 
-// Rows of at most 64 segments exchange directly (one lane per segment).
-constexpr int PRES_DIRECT_MAX = 64;
-
-template <int ACC, bool DIRECT>
+template <int ACC, int BLOCK, int LOG2>
 hipError_t plain_resident_acc(const RowDesc& d, const PlainResidentWs& w, hipStream_t s) {
-  const unsigned grid = (unsigned)((d.n + (int64_t(1) << PRES_LOG2) - 1) >> PRES_LOG2);
+  const unsigned grid = (unsigned)((d.n + (int64_t(1) << LOG2) - 1) >> LOG2);
 #define NRM_PR(I, O) \
-  hipLaunchKernelGGL((plain_resident_kernel<I, O, ACC, DIRECT>), dim3(grid), dim3(PRES_BLOCK), 0, s, d, w)
+  hipLaunchKernelGGL((plain_resident_kernel<I, O, ACC, BLOCK, LOG2>), dim3(grid), dim3(BLOCK), 0, s, d, w)
   switch (d.in_dt * 3 + d.out_dt) {
     case NRM_F32 * 3 + NRM_F32: NRM_PR(NRM_F32, NRM_F32); break;
     case NRM_F32 * 3 + NRM_BF16: NRM_PR(NRM_F32, NRM_BF16); break;
@@ -1133,11 +1139,18 @@ hipError_t plain_resident_acc(const RowDesc& d, const PlainResidentWs& w, hipStr
   return hipGetLastError();
 }
 
+template <int ACC>
+hipError_t plain_resident_size(const RowDesc& d, const PlainResidentWs& w, hipStream_t s) {
+  return d.n <= PRES_SHORT_MAX ? plain_resident_acc<ACC, PRES_BLOCK, PRES_LOG2>(d, w, s)
+                               : plain_resident_acc<ACC, RES_BLOCK, RES_LOG2>(d, w, s);
+}
 
 }  // namespace
 
 int64_t small_capacity(int) { return SMALL_ELEMS; }
-int64_t plain_resident_capacity() { return (int64_t)PRES_MAX_SEGMENTS << PRES_LOG2; }
+int64_t plain_resident_capacity(int acc) {
+  return ((int64_t)PRES_MAX_SEGMENTS << RES_LOG2) >> (acc == NRM_ACC_KAHAN ? 1 : 0);
+}
 
 hipError_t launch_plain_resident(const void* in, int in_dt, void* out, int out_dt, int64_t n, int acc,
                                  const PlainResidentWs& w, hipStream_t s) {
@@ -1147,10 +1160,7 @@ hipError_t launch_plain_resident(const void* in, int in_dt, void* out, int out_d
   d.n = n;
   d.in_dt = in_dt;
   d.out_dt = out_dt;
-  const bool direct = ((n + (int64_t(1) << PRES_LOG2) - 1) >> PRES_LOG2) <= PRES_DIRECT_MAX;
-  if (acc == NRM_ACC_KAHAN)
-    return direct ? plain_resident_acc<NRM_ACC_KAHAN, true>(d, w, s) : plain_resident_acc<NRM_ACC_KAHAN, false>(d, w, s);
-  return direct ? plain_resident_acc<NRM_ACC_F32, true>(d, w, s) : plain_resident_acc<NRM_ACC_F32, false>(d, w, s);
+  return acc == NRM_ACC_KAHAN ? plain_resident_size<NRM_ACC_KAHAN>(d, w, s) : plain_resident_size<NRM_ACC_F32>(d, w, s);
 }
 
 hipError_t launch_small(const void* in, int in_dt, void* out, int out_dt, int64_t n, int acc, float* sum_out,

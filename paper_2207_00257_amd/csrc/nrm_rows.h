@@ -216,7 +216,7 @@ struct ResExchange {
   uint32_t ep;                // this call's number
   int* error;                 // device error word (NRM_DEVERR_STALL)
   unsigned long long* stall;  // the number of the last call in which a wait gave up
-  unsigned long long* call;   // when set: the call counter the last arrival moves on
+  unsigned long long* call;   // DIRECT: the call counter the last arrival moves on
 };
 
 template <int ACC>
@@ -395,7 +395,7 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
       // after this block's reads of the tags: the last one moves the call on
       if (__hip_atomic_fetch_add(x.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nseg - 1) {
         __hip_atomic_store(x.arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (x.call) __hip_atomic_fetch_add(x.call, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(x.call, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   } else if (t < 64) {
@@ -411,10 +411,7 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
       // to 0 for the next call, and the merged total is published once
       if (t == 0) __hip_atomic_store(x.arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       total = gather_row<ACC, PER_LANE>(x, nseg);
-      if (t == 0) {
-        publish_tagged<ACC>(x.total, x.ep, total);
-        if (x.call) __hip_atomic_fetch_add(x.call, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      if (t == 0) publish_tagged<ACC>(x.total, x.ep, total);
     } else if (t == 0) {
       total = wait_tagged<ACC>(x, x.total);
     }
