@@ -136,8 +136,7 @@ typedef struct {
   int32_t unroll;      /* tile sums: 16-byte vectors per thread per iteration: 1, 2, 4, 8 */
   int32_t map_unroll;  /* tile divides: 16-byte vectors per thread per iteration: 1, 2, 4, 8 */
   int32_t grid;        /* blocks of phase 1 (sums, single-pass rows) */
-  int32_t tile_log2;   /* a long row is cut into tiles of 2^tile_log2 elements: 10..22 (in the resident
-                          rows' kernel at most 2^21) */
+  int32_t tile_log2;   /* a long row is cut into tiles of 2^tile_log2 elements: 10..22 */
   int32_t short_regs;  /* 16-byte vectors per thread held in registers by a single-pass row:
                           1, 2, 4 or 8; rows with n <= block * short_regs * 4 take one pass
                           (one read, one write) */
@@ -157,7 +156,7 @@ typedef struct {
                                 single-pass or tile path) */
   int32_t resident_grid;     /* persistent 512-thread blocks of the resident rows' kernel, 1..2^20 and
                                 at least resident_segments: a row's blocks wait for each other, so the
-                                device must be able to run that many of them at once (two per CU fit;
+                                device must be able to run that many of them at once (three per CU fit;
                                 fewer are launched for a batch that cannot use them) */
   int32_t wave_max;          /* 0..2048: a row of 0 < n <= wave_max elements is taken by one wavefront
                                 (64 lanes), or for n <= 256 by a quarter of one (16 lanes, four such

@@ -128,6 +128,9 @@ __device__ __forceinline__ uint32_t wave_scan32(uint32_t x, int lane) {
   return x;
 }
 
+// Entries of a resident row.
+__device__ __forceinline__ int64_t row_segments(int64_t n) { return (n + (int64_t(1) << RES_LOG2) - 1) >> RES_LOG2; }
+
 // The call number travels in two words so that no launch reads a word that
 // it writes: batch_rows_kernel reads CNT_CALL and leaves CNT_CALL + 1 in
 // CNT_CALL_RUN, which the launches after it read; the last of them copies
@@ -216,16 +219,19 @@ __device__ __forceinline__ void single_pass(const RowDesc& d, Acc<ACC>* slots, R
 
 // Sum of elements [b, e) of a row; valid in thread 0. NT: non-temporal loads
 // (a temporal tile stays in the last-level cache for phase 2).
-template <int DTI, int ACC, int U, bool NT>
+// NA independent chains per thread, each vector's elements dealt to them in
+// turn: the bits depend on NA, not on U.
+template <int DTI, int ACC, int U, bool NT, int NA>
 __device__ __forceinline__ Acc<ACC> tile_reduce(const char* in_row, int64_t b, int64_t e,
                                                 Acc<ACC>* slots) {
   constexpr int VEC = Elem<DTI>::VEC;
-  constexpr int NA = accumulators(DTI, ACC, U);
-  constexpr int FLUSH = CHAIN_ADDS / adds_per_iteration(DTI, ACC, U);
+  const int t = thread_index();
+  static_assert(CHAIN_ADDS * NA % (U * VEC) == 0 && U * VEC % NA == 0, "whole iterations between flushes");
+  constexpr int FLUSH = CHAIN_ADDS * NA / (U * VEC);
   const char* seg = in_row + b * Elem<DTI>::SIZE;
   const int n = (int)(e - b);
   const Geom g = geometry<DTI>(seg, n);
-  const u4* p = reinterpret_cast<const u4*>(seg + g.head * Elem<DTI>::SIZE) + threadIdx.x;
+  const u4* p = reinterpret_cast<const u4*>(seg + g.head * Elem<DTI>::SIZE) + t;
   const int B = blockDim.x, step = B * U;
   Acc<ACC> acc[NA];
 #pragma unroll
@@ -235,10 +241,10 @@ __device__ __forceinline__ Acc<ACC> tile_reduce(const char* in_row, int64_t b, i
   int since_flush = 0;
   // the unaligned head and the short tail, loaded before the stream so their
   // latency overlaps it
-  const bool has_head = (int)threadIdx.x < g.head;
-  const bool has_tail = (int)threadIdx.x < n - g.tail_begin;
-  const float xh = has_head ? load_one<DTI>(seg, threadIdx.x) : 0.0f;
-  const float xt = has_tail ? load_one<DTI>(seg, g.tail_begin + threadIdx.x) : 0.0f;
+  const bool has_head = t < g.head;
+  const bool has_tail = t < n - g.tail_begin;
+  const float xh = has_head ? load_one<DTI>(seg, t) : 0.0f;
+  const float xt = has_tail ? load_one<DTI>(seg, g.tail_begin + t) : 0.0f;
   for (int base = 0; base < g.nvec; base += step) {
     if (base + step <= g.nvec) {
       u4 r[U];
@@ -275,7 +281,7 @@ __device__ __forceinline__ Acc<ACC> tile_reduce(const char* in_row, int64_t b, i
     } else {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        if (base + u * B + (int)threadIdx.x < g.nvec) {
+        if (base + u * B + t < g.nvec) {
           float x[VEC];
           widen<DTI>(load_vec<NT>(p + base + u * B), x);
 #pragma unroll
@@ -304,6 +310,7 @@ __device__ __forceinline__ Acc<ACC> tile_reduce(const char* in_row, int64_t b, i
 template <int DTI, int DTO, int U, class F>
 __device__ __forceinline__ void tile_map(const RowDesc& d, int64_t b, int64_t e, const F& f) {
   constexpr int VEC = Elem<DTI>::VEC;
+  const int t = thread_index();
   const char* in_seg = d.in + b * Elem<DTI>::SIZE;
   char* out_seg = d.out + b * Elem<DTO>::SIZE;
   const int n = (int)(e - b);
@@ -311,13 +318,13 @@ __device__ __forceinline__ void tile_map(const RowDesc& d, int64_t b, int64_t e,
   const u4* body = reinterpret_cast<const u4*>(in_seg + g.head * Elem<DTI>::SIZE);
   const bool vec_ok = out_vector_ok<DTI, DTO>(out_seg, g.head);
   const int B = blockDim.x, step = B * U;
-  const bool has_head = (int)threadIdx.x < g.head;
-  const int ti = g.tail_begin + (int)threadIdx.x;
+  const bool has_head = t < g.head;
+  const int ti = g.tail_begin + t;
   const bool has_tail = ti < n;
-  const float xh = has_head ? load_one<DTI>(in_seg, threadIdx.x) : 0.0f;
+  const float xh = has_head ? load_one<DTI>(in_seg, t) : 0.0f;
   const float xt = has_tail ? load_one<DTI>(in_seg, ti) : 0.0f;
   for (int base = 0; base < g.nvec; base += step) {
-    const int v0 = base + (int)threadIdx.x;
+    const int v0 = base + t;
     if (base + step <= g.nvec) {
       u4 r[U];
 #pragma unroll
@@ -343,7 +350,7 @@ __device__ __forceinline__ void tile_map(const RowDesc& d, int64_t b, int64_t e,
       }
     }
   }
-  if (has_head) store_one<DTO>(out_seg, threadIdx.x, f(xh));
+  if (has_head) store_one<DTO>(out_seg, t, f(xh));
   if (has_tail) store_one<DTO>(out_seg, ti, f(xt));
 }
 
@@ -372,18 +379,21 @@ __device__ __forceinline__ void dispatch_single(const RowDesc& d, Acc<ACC>* slot
   }
 }
 
-template <int ACC, int U, bool NT>
+// NA 0: one chain per element of an iteration, as the plain reduce has them.
+template <int ACC, int U, bool NT, int NA = 0>
 __device__ __forceinline__ Acc<ACC> dispatch_tile_reduce(const RowDesc& d, int64_t b, int64_t e,
                                                          Acc<ACC>* slots) {
+#define NRM_TR(I) return tile_reduce<I, ACC, U, NT, NA ? NA : accumulators(I, ACC, U)>(d.in, b, e, slots)
   if constexpr (ACC == ACC_SOFTMAX) {
-    return tile_reduce<NRM_F32, ACC, U, NT>(d.in, b, e, slots);
+    NRM_TR(NRM_F32);
   } else {
     switch (d.in_dt) {
-      case NRM_F32: return tile_reduce<NRM_F32, ACC, U, NT>(d.in, b, e, slots);
-      case NRM_BF16: return tile_reduce<NRM_BF16, ACC, U, NT>(d.in, b, e, slots);
-      default: return tile_reduce<NRM_F16, ACC, U, NT>(d.in, b, e, slots);
+      case NRM_F32: NRM_TR(NRM_F32);
+      case NRM_BF16: NRM_TR(NRM_BF16);
+      default: NRM_TR(NRM_F16);
     }
   }
+#undef NRM_TR
 }
 
 template <int ACC, int U>
@@ -410,7 +420,13 @@ __device__ __forceinline__ void dispatch_tile_map(const RowDesc& d, int64_t b, i
 // ---- the long rows' tiles and the resident rows, persistently -------------------------------
 
 constexpr int TILE_U = 4;      // tile sums: vectors per thread per iteration
+constexpr int TILE_NA = 8;     // and chains
 constexpr int TILE_MAP_U = 4;  // tile divides
+// A tile is summed in parts of at most this many elements: a thread's tree
+// then has height 36 (16 + 1 additions in a chain, 3 merges of its 8 chains,
+// 16 of its totals), the whole row's 36 + 9 (wavefront, block) + 16
+// (gather_tiles), and up to 4 more for tiles of several parts.
+constexpr int64_t TILE_PART = int64_t(1) << 20;
 // elements of one unit of the divide: one block-iteration of 4-byte elements
 constexpr int64_t MAP_UNIT = (int64_t)RES_BLOCK * TILE_MAP_U * 4;
 
@@ -445,6 +461,14 @@ __device__ __forceinline__ Acc<ACC> gather_tiles(const ResExchange& x, int64_t c
   return v;
 }
 
+// The entries that one block of batch_rows_kernel appended: where in the list,
+// and which in row order.
+struct ListRange {
+  int64_t base;
+  uint32_t start, count;
+};
+static_assert(ORDERED_BLOCKS == RES_BLOCK, "one range per thread");
+
 // Persistent blocks: the units are the long rows' tile sums, then the
 // segments of the resident rows, both taken one at a time from a counter in
 // list order; then the long rows' tiles once more, in units of MAP_UNIT
@@ -455,30 +479,36 @@ __device__ __forceinline__ Acc<ACC> gather_tiles(const ResExchange& x, int64_t c
 // like the resident rows'.
 //
 // HBM bounds it: resident rows move 8 bytes per binary32 element, long rows
-// 12. The tiles of the divide are dealt statically because nothing waits for
+// 12. 4096 rows of up to 2^20 binary32 (3.43 GB) take 572 us per call with three
+// blocks per CU (80 registers; with the plain reduce's 16 chains in the tile
+// sums 128 and two blocks, 616 us; four blocks spilled: 597-622 us), BF16 ones
+// 404 against 478 us, the latency of their smaller segments (claim, entry,
+// elements, exchange) not hidden. The tiles of the divide are dealt statically because nothing waits for
 // them, and in units of 2^13 elements so that the last round of 512 blocks is
 // short (whole tiles of 2^15 left up to half of the blocks idle in it).
 template <int ACC>
-__global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(4, 4))) batch_resident_kernel(BatchArgs a) {
+__global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(6, 6))) batch_resident_kernel(BatchArgs a) {
   __shared__ Acc<ACC> slots[MAX_WAVES];
   __shared__ RowRes s_bcast;
   __shared__ int64_t s_claim;
   __shared__ Acc<ACC> rounds[TILE_ROUNDS];
   __shared__ int s_last;
   __shared__ uint32_t s_scan[RES_BLOCK / 64];
+  __shared__ ListRange s_range[ORDERED_BLOCKS];
   __shared__ int64_t s_pos;
   unsigned long long* counter = reinterpret_cast<unsigned long long*>(a.cnt + CNT_TAKEN);
+  auto take = [&] {
+    return (int64_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   // every word the start needs in one round trip: both sets of counters, of
   // which the call's number picks one
-  if (threadIdx.x == 0)
-    s_claim = (int64_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) s_claim = take();
   const int64_t call = a.cnt[CNT_CALL_RUN], ordered = a.cnt[CNT_ORDERED];
   const int64_t* set0 = list_counters(a, 0);
   const int64_t* set1 = list_counters(a, 1);
   const int64_t t0 = set0[LIST_TILES * CNT_LINE], s0 = set0[LIST_SHORT * CNT_LINE];
   const int64_t t1 = set1[LIST_TILES * CNT_LINE], s1 = set1[LIST_SHORT * CNT_LINE];
-  BlockShorts mine{0, 0};
-  if (threadIdx.x < ORDERED_BLOCKS) mine = a.block_shorts[threadIdx.x];
+  const BlockShorts mine = a.block_shorts[threadIdx.x];
   int64_t n_long = call & 1 ? t1 : t0, n_short = call & 1 ? s1 : s0;
   // (entries past the capacity were not written; in row order they are passed
   // over one by one)
@@ -494,23 +524,24 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
   // order in which the blocks of batch_rows_kernel appended them: thread t
   // holds block t's range of the list and where it starts in row order.
   // (4096 rows, 1.7 GB: 642 us in memory order, 666 us shuffled.)
-  uint32_t starts = 0;
   if (ordered > 0) {
-    if ((int64_t)threadIdx.x >= ordered) mine.count = 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t incl = wave_scan32((uint32_t)mine.count, lane);
+    const uint32_t count = (int64_t)threadIdx.x < ordered ? (uint32_t)mine.count : 0u;
+    const uint32_t incl = wave_scan32(count, lane);
     if (lane == 63) s_scan[wave] = incl;
     lds_barrier();
-    starts = incl - (uint32_t)mine.count;
-    for (int w = 0; w < wave; ++w) starts += s_scan[w];
+    uint32_t start = incl - count;
+    for (int w = 0; w < wave; ++w) start += s_scan[w];
+    s_range[threadIdx.x] = ListRange{mine.base, start, count};
   }
   lds_barrier();
   int64_t u = uniform64(s_claim);
   while (u < units) {
     int64_t pos = u - n_long;  // in the list of segments
     if (pos >= 0 && ordered > 0) {
-      const uint32_t off = (uint32_t)pos - starts;
-      if ((uint32_t)pos >= starts && off < (uint32_t)mine.count) s_pos = mine.base + off;
+      const ListRange r = s_range[threadIdx.x];
+      const uint32_t off = (uint32_t)pos - r.start;
+      if ((uint32_t)pos >= r.start && off < r.count) s_pos = r.base + off;
       lds_barrier();
       pos = uniform64(s_pos);
     }
@@ -525,8 +556,15 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
         const int64_t e = b + a.tile < d.n ? b + a.tile : d.n;
         // the last keep_tiles tiles are read with a temporal hint: the
         // divide finds them in the last-level cache
-        const Acc<ACC> p = u >= n_long - a.keep_tiles ? dispatch_tile_reduce<ACC, TILE_U, false>(d, b, e, slots)
-                                                      : dispatch_tile_reduce<ACC, TILE_U, true>(d, b, e, slots);
+        const bool keep = u >= n_long - a.keep_tiles;
+        Acc<ACC> p;
+        p.zero();
+        for (int64_t c = b; c < e; c += TILE_PART) {
+          const int64_t ce = c + TILE_PART < e ? c + TILE_PART : e;
+          p.merge(keep ? dispatch_tile_reduce<ACC, TILE_U, false, TILE_NA>(d, c, ce, slots)
+                       : dispatch_tile_reduce<ACC, TILE_U, true, TILE_NA>(d, c, ce, slots));
+          if (ce < e) lds_barrier();  // slots are reused
+        }
         const ResExchange x{a.tile_tagged + 2 * first, a.tile_total + 2 * first, a.tile_arrivals + first, ep, a.error,
                             stall, nullptr};
         const int64_t count = (d.n + a.tile - 1) >> a.tile_log2;
@@ -556,8 +594,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
     // the next unit once this one is done (claiming it as soon as the row's
     // sum was known, to overlap the claim with the writes, measured slower)
     lds_barrier();  // slots, s_bcast and s_claim are reused
-    if (threadIdx.x == 0)
-      s_claim = (int64_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) s_claim = take();
     lds_barrier();
     u = uniform64(s_claim);
   }
@@ -974,8 +1011,7 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
     if (wave == 0) {
       const bool listed = n > h.run_max, is_long = listed && n > a.short_max;
       const uint32_t tiles = is_long ? (uint32_t)long_tiles(n, a.short_max, a.tile_log2) : 0u;
-      const uint32_t shorts =
-          listed && !is_long ? (a.res_on ? (uint32_t)((n + (int64_t(1) << RES_LOG2) - 1) >> RES_LOG2) : 1u) : 0u;
+      const uint32_t shorts = listed && !is_long ? (a.res_on ? (uint32_t)row_segments(n) : 1u) : 0u;
       const uint32_t it = wave_scan32(tiles, lane), is = wave_scan32(shorts, lane);
       if (lane < ROWS_MAX) s_at[lane] = is_long ? it - tiles : is - shorts;
       if (lane == 63) {
@@ -1001,7 +1037,7 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
       const int32_t row = (int32_t)(r0 + j);
       const bool is_long = x.n > a.short_max;
       const int64_t count = is_long ? long_tiles(x.n, a.short_max, a.tile_log2)
-                            : a.res_on ? (x.n + (int64_t(1) << RES_LOG2) - 1) >> RES_LOG2
+                            : a.res_on ? row_segments(x.n)
                                        : 1;
       const int64_t first = (is_long ? s_base_tiles : s_base_shorts) + s_at[j];
       Item* to = is_long ? a.tiles : a.shorts;

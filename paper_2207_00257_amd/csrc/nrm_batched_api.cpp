@@ -53,9 +53,9 @@ nrm_batch_params default_batch_params() {
   p.map_grid = 1024;
   p.keep_mib = 256;
   // rows up to 64 segments of 2^14 elements (2^20) are held on chip between
-  // their read and their write; two 512-thread blocks per CU
+  // their read and their write; three 512-thread blocks per CU
   p.resident_segments = 64;
-  p.resident_grid = 512;
+  p.resident_grid = 768;
   // rows of up to 2048 elements one per wavefront, 16 wavefronts per CU
   p.wave_max = 2048;
   p.wave_grid = 1024;
@@ -231,15 +231,10 @@ int64_t items_bound(const nrm_batch_params& p, int64_t rows, int64_t elems) {
   return rows + ceil_div(std::max<int64_t>(elems, 0), int64_t(1) << lg);
 }
 
-// The tile size the kernels use: 2^tile_log2, in the resident rows' kernel at
-// most 2^21 (its 512 threads then keep a thread's summation tree within the
-// height bound whatever the block size the parameters were checked with).
-int tile_log2_of(const nrm_batch_params& p) { return p.resident_segments > 0 ? std::min(p.tile_log2, 21) : p.tile_log2; }
-
 BatchArgs args_of(const nrm_ctx* c) {
   BatchArgs a = c->batch.args;
   const nrm_batch_params& p = c->bparams;
-  a.tile_log2 = tile_log2_of(p);
+  a.tile_log2 = p.tile_log2;
   a.tile = int64_t(1) << a.tile_log2;
   a.short_max = short_max_of(p);
   // tiles counted at 4 bytes per element: at most keep_mib MiB for any dtype
@@ -261,6 +256,9 @@ BatchPlan plan_of(const nrm_ctx* c, const BatchHeader& h, int64_t rows, int64_t 
   // no more blocks than a small batch can list entries: a listed row of more
   // than 2^RES_LOG2 elements has fewer than two entries per 2^RES_LOG2 of them
   p.res_grid = std::min<int64_t>(q.resident_grid, (h.run_max > 0 ? 0 : rows) + 2 * (elems >> nrm::RES_LOG2) + 1);
+  // long rows stream better from two blocks per CU (2^26 binary32 in one row:
+  // 145 against 148 us; 16 rows of up to 2^24: 64.3 and 66.8 us)
+  if (elems / rows > short_max_of(q)) p.res_grid = std::min<int64_t>(p.res_grid, std::max(512, q.resident_segments));
   p.block = q.block;
   p.unroll = q.unroll;
   p.map_unroll = q.map_unroll;
@@ -576,7 +574,7 @@ int nrm_normalize_rows(nrm_ctx* c, const nrm_row* rows, int64_t nrows, int accum
     if (st != NRM_OK) return st;
   }
   nrm::CtxLock lk(c->mu);
-  if (longest > (int64_t(1) << tile_log2_of(c->bparams)) * nrm::MAX_ROW_TILES)
+  if (longest > (int64_t(1) << c->bparams.tile_log2) * nrm::MAX_ROW_TILES)
     return fail(NRM_EINVAL, "row too long for the batched path's tile size");
   DeviceGuard g(c->device);
   int st = reserve(c, nrows, items_bound(c->bparams, nrows, total));

@@ -15,6 +15,15 @@ namespace {
 
 using namespace dev;
 
+// The thread's index, opaque to the compiler: used inside a loop over segments
+// it keeps what each dtype's code derives from it from being computed once
+// before the loop and held there, in registers that the segments need.
+__device__ __forceinline__ int thread_index() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // ---- geometry of one contiguous segment --------------------------------------
 
 // A segment's vector body starts on a 128-byte boundary (one cache line), so
@@ -335,7 +344,7 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
   // chains per thread: 8 binary32, 4 of the two-float kinds (registers)
   constexpr int NA_MAX = ACC == NRM_ACC_F32 ? 8 : 4;
   constexpr int NA = KB * VEC < NA_MAX ? KB * VEC : NA_MAX;
-  const int t = threadIdx.x;
+  const int t = thread_index();
   constexpr int S = 1 << LOG2;
   const int64_t b = (int64_t)seg << LOG2;
   const int n = d.n - b < S ? (int)(d.n - b) : S;
