@@ -10,6 +10,7 @@ device); this module passes their raw pointers through the C ABI.
 from __future__ import annotations
 
 import ctypes
+import struct
 from typing import Optional
 
 from . import _lib as L
@@ -17,30 +18,50 @@ from . import _lib as L
 _ACCUM = {"f32": L.NRM_ACC_F32, "kahan": L.NRM_ACC_KAHAN}
 
 
-def _dtype_code(t) -> int:
+# torch's dtypes and its current-stream lookup, bound on first use (the library
+# itself does not need torch)
+_codes: dict = {}
+_raw_stream = None
+
+
+def _bind_torch():
+    global _raw_stream
     import torch
 
-    codes = {torch.float32: L.NRM_F32, torch.bfloat16: L.NRM_BF16, torch.float16: L.NRM_F16}
-    if t.dtype not in codes:
+    _codes.update({torch.float32: L.NRM_F32, torch.bfloat16: L.NRM_BF16, torch.float16: L.NRM_F16})
+    # the current stream's handle without a Stream object around it (0.1 us
+    # instead of 1.5 us per call), where this torch has it
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
+def _dtype_code(t) -> int:
+    if not _codes:
+        _bind_torch()
+    code = _codes.get(t.dtype)
+    if code is None:
         raise TypeError("unsupported dtype %s (float32, bfloat16, float16)" % t.dtype)
-    return codes[t.dtype]
+    return code
 
 
 def _stream_of(t) -> int:
-    import torch
+    if _raw_stream is None:
+        _bind_torch()
+    return _raw_stream(t.get_device())
 
-    return torch.cuda.current_stream(t.device).cuda_stream
 
-
-def _check_tensors(out, inp):
+def _check_tensors(out, inp) -> int:
+    """Check a pair of tensors; returns their length."""
     if not inp.is_cuda or not out.is_cuda:
         raise ValueError("normalize needs device tensors (the library has no CPU path)")
-    if inp.device != out.device:
+    if inp.get_device() != out.get_device():
         raise ValueError("in and out are on different devices")
     if not inp.is_contiguous() or not out.is_contiguous():
         raise ValueError("in and out must be contiguous")
-    if inp.numel() != out.numel():
+    n = inp.numel()
+    if n != out.numel():
         raise ValueError("in and out differ in length")
+    return n
 
 
 class Context:
@@ -143,14 +164,29 @@ def normalize(out, inp, accum: str = "f32", ctx: Optional[Context] = None, strea
 
     inp: float32 / bfloat16 / float16 device tensor; out: same length, any of
     those dtypes (out may be inp itself). accum: "f32" or "kahan"."""
-    _check_tensors(out, inp)
+    n = _check_tensors(out, inp)
     if accum not in _ACCUM:
         raise ValueError("accum must be 'f32' or 'kahan'")
     s = _stream_of(inp) if stream is None else stream
     st = L.lib().nrm_normalize_ex(ctx.handle if ctx else None, out.data_ptr(), _dtype_code(out),
-                                  inp.data_ptr(), _dtype_code(inp), inp.numel(), _ACCUM[accum], s)
-    L.check(st, "nrm_normalize_ex")
+                                  inp.data_ptr(), _dtype_code(inp), n, _ACCUM[accum], s)
+    if st:
+        L.check(st, "nrm_normalize_ex")
     return out
+
+
+def _check_offsets(offsets, inp) -> int:
+    """Check CSR offsets; returns the number of rows."""
+    import torch
+
+    if offsets.dtype != torch.int64 or not offsets.is_cuda or not offsets.is_contiguous():
+        raise ValueError("offsets must be a contiguous int64 device tensor")
+    if offsets.get_device() != inp.get_device():
+        raise ValueError("offsets is on another device")
+    rows = offsets.numel() - 1
+    if rows < 0:
+        raise ValueError("offsets needs rows + 1 >= 1 entries")
+    return rows
 
 
 def normalize_batched(out, inp, offsets, accum: str = "f32", ctx: Optional[Context] = None,
@@ -159,23 +195,16 @@ def normalize_batched(out, inp, offsets, accum: str = "f32", ctx: Optional[Conte
     (and the same slice of out), normalized on its own. offsets: int64 device
     tensor of rows + 1 entries. The device checks every row against the
     tensors' length; see device_error()."""
-    import torch
-
-    _check_tensors(out, inp)
+    n = _check_tensors(out, inp)
     if accum not in _ACCUM:
         raise ValueError("accum must be 'f32' or 'kahan'")
-    if offsets.dtype != torch.int64 or not offsets.is_cuda or not offsets.is_contiguous():
-        raise ValueError("offsets must be a contiguous int64 device tensor")
-    if offsets.device != inp.device:
-        raise ValueError("offsets is on another device")
-    rows = offsets.numel() - 1
-    if rows < 0:
-        raise ValueError("offsets needs rows + 1 >= 1 entries")
+    rows = _check_offsets(offsets, inp)
     s = _stream_of(inp) if stream is None else stream
     st = L.lib().nrm_normalize_batched_ex(ctx.handle if ctx else None, out.data_ptr(), _dtype_code(out),
                                           inp.data_ptr(), _dtype_code(inp), offsets.data_ptr(), rows,
-                                          inp.numel(), _ACCUM[accum], s)
-    L.check(st, "nrm_normalize_batched_ex")
+                                          n, _ACCUM[accum], s)
+    if st:
+        L.check(st, "nrm_normalize_batched_ex")
     return out
 
 
@@ -190,13 +219,7 @@ def softmax_batched(out, inp, offsets, lse=None, ctx: Optional[Context] = None, 
     _check_tensors(out, inp)
     if inp.dtype != torch.float32 or out.dtype != torch.float32:
         raise ValueError("softmax_batched takes float32 in and out")
-    if offsets.dtype != torch.int64 or not offsets.is_cuda or not offsets.is_contiguous():
-        raise ValueError("offsets must be a contiguous int64 device tensor")
-    if offsets.device != inp.device:
-        raise ValueError("offsets is on another device")
-    rows = offsets.numel() - 1
-    if rows < 0:
-        raise ValueError("offsets needs rows + 1 >= 1 entries")
+    rows = _check_offsets(offsets, inp)
     lse_ptr = None
     if lse is not None:
         if lse.dtype != torch.float32 or not lse.is_cuda or not lse.is_contiguous() or lse.numel() != rows:
@@ -281,23 +304,23 @@ def normalize_rows(pairs, accum: str = "f32", ctx: Optional[Context] = None, str
     if accum not in _ACCUM:
         raise ValueError("accum must be 'f32' or 'kahan'")
     pairs = list(pairs)
-    table = (L.NrmRow * max(1, len(pairs)))()
+    fields = []
     dev = None
-    for i, (out, inp) in enumerate(pairs):
-        _check_tensors(out, inp)
-        dev = inp.device if dev is None else dev
-        if inp.device != dev:
+    for out, inp in pairs:
+        n = _check_tensors(out, inp)
+        index = inp.get_device()
+        dev = index if dev is None else dev
+        if index != dev:
             raise ValueError("rows on different devices")
-        table[i].in_ = inp.data_ptr()
-        table[i].out = out.data_ptr()
-        table[i].n = inp.numel()
-        table[i].in_dtype = _dtype_code(inp)
-        table[i].out_dtype = _dtype_code(out)
+        fields += (inp.data_ptr(), out.data_ptr(), n, _dtype_code(inp), _dtype_code(out))
     if not pairs:
         return
+    # the rows' descriptors, laid out as NrmRow
+    table = (L.NrmRow * len(pairs)).from_buffer_copy(struct.pack("=" + "QQqii" * len(pairs), *fields))
     s = _stream_of(pairs[0][1]) if stream is None else stream
     st = L.lib().nrm_normalize_rows(ctx.handle if ctx else None, table, len(pairs), _ACCUM[accum], s)
-    L.check(st, "nrm_normalize_rows")
+    if st:
+        L.check(st, "nrm_normalize_rows")
 
 
 def device_error(ctx: Optional[Context] = None, stream: Optional[int] = None) -> int:
