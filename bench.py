@@ -373,7 +373,7 @@ def main():
 
 def bench_ragged(args):
     """Ragged batched workload: one step = one batched call over 4096 rows
-    (planner, resident rows, tile phases, replayed from a captured hipGraph).
+    (the rows, then the lists of the longer ones, replayed from a captured hipGraph).
     Also times the basic C form on the default context, and the same rows as
     one plain normalize call per row, for comparison."""
     import ctypes

@@ -183,7 +183,7 @@ def sweep(n: int, in_dtype="f32", out_dtype="f32", accum="f32", reps=5, quick=Fa
 def sweep_batched(rows=4096, seed=4, reps=3, quick=False, log=print):
     """Sweep the batched path's launch shape on the ragged workload (rows with
     log-uniform lengths in [32, 2^20], LogNormal(0,1) FP32), timing whole
-    calls (planner, short rows, resident rows, tile phases) with the
+    calls (the rows, then the lists of the longer ones) with the
     library's events: first the resident rows' limit and grid, then the
     short rows' (one per wavefront) limit and grid, then, when some row of
     the workload is longer than the resident limit, the tile phases'
