@@ -941,9 +941,15 @@ __device__ __forceinline__ void dispatch_quarter(const RowDesc& d, float* lse) {
 // waits for another, so the grid is as large as the batch and streams the rows
 // in dispatch order.
 //
-// First each wavefront runs its own rows of at most wave_max elements (those
-// of at most QUARTER_MAX all at once, 16 lanes each). Behind the block's one
-// barrier it then appends its rows of more than run_max elements to the lists:
+// First each wavefront runs its own rows of at most QUARTER_MAX elements, all
+// at once on 16 lanes each, then rows of at most wave_max: with one row per
+// wavefront its own, with four the block's, dealt out in turn, since one
+// wavefront may hold four of them and its neighbour none. For that the block's
+// barrier stands before the rows there (200,000 rows of up to 4096: 163 us, 175
+// with own rows only; 2^20 rows of 17: 118 and 138; 2^20 of 256: 346 and 353);
+// with one row each it stands behind them (100,000 rows of 100 to 3000: 149 us,
+// before them 159 to 176; rows of 2048 alone are the other way: 393 and 356).
+// It then appends its rows of more than run_max elements to the lists:
 // the segments of a resident row (one for a row of at most 2^RES_LOG2 elements;
 // resident rows off, a single-pass row's one entry) to `shorts`, a long row's
 // tiles to `tiles`; a row's entries are consecutive, the order of the rows in
@@ -951,7 +957,7 @@ __device__ __forceinline__ void dispatch_quarter(const RowDesc& d, float* lse) {
 // run_max one after the other.
 //
 // What bounds it: with many short rows HBM (2^20 rows of 256 binary32, 2.16 GB:
-// 357 us per call, 6.0 TB/s, against 564 us in six launches over planned
+// 346 us per call, 6.2 TB/s, against 564 us in six launches over planned
 // tables), with few the launch and the chain of dependent loads (offsets,
 // elements; 64 rows of up to 256: 4.1 us per call). 80 registers, three blocks
 // per CU: spilling any of them cost more than a block less (2^20 rows of 256:
@@ -994,19 +1000,25 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
         s_rows[own] = d;
       }
     }
+    if (rw > 1) lds_barrier();
     if (d.n > 0 && d.n <= QUARTER_MAX && d.n <= a.wave_max)
       dispatch_quarter<ACC>(d, h.lse ? h.lse + (r0 + own) : nullptr);
   }
-  for (int g = 0; g < rw; ++g) {
-    const int j = wave * rw + g;  // written by this wavefront
-    if (j >= here) break;
-    const int64_t n = uniform64(s_rows[j].n);
-    if (n > QUARTER_MAX && n <= a.wave_max)
-      dispatch_wave<ACC>(uniform_desc(s_rows[j]), h.lse ? h.lse + (r0 + j) : nullptr);
-  }
-  lds_barrier();
   // every wavefront sees the same rows: lane j the block's row j
-  int64_t n = lane < here ? s_rows[lane].n : 0;
+  int64_t n = lane < here && (rw > 1 || lane == wave) ? s_rows[lane].n : 0;
+  {
+    const uint32_t waves = (uint32_t)__ballot(n > QUARTER_MAX && n <= a.wave_max);
+    uint32_t k = rw > 1 ? 0 : wave;
+    for (uint32_t m = waves; m; m &= m - 1, ++k) {
+      if (k % ROWS_WAVES != wave) continue;
+      const int j = __builtin_ctz(m);
+      dispatch_wave<ACC>(uniform_desc(s_rows[j]), h.lse ? h.lse + (r0 + j) : nullptr);
+    }
+  }
+  if (rw == 1) {
+    lds_barrier();
+    n = lane < here ? s_rows[lane].n : 0;
+  }
   if (n <= a.wave_max) n = 0;
   const uint32_t kept = (uint32_t)__ballot(n > 0), list = (uint32_t)__ballot(n > h.run_max);
   if (list) {
