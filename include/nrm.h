@@ -327,8 +327,8 @@ int nrm_normalize_batched_ex(nrm_ctx* ctx, void* out, int out_dtype, const void*
                              const int64_t* offsets, int64_t rows, int64_t capacity, int accum,
                              void* stream);
 
-/* Row softmax and log-sum-exp of a ragged batch, on the same planner and
- * persistent phases as the batched normalize. Softmax is one of the
+/* Row softmax and log-sum-exp of a ragged batch, in the same two
+ * launches as the batched normalize. Softmax is one of the
  * aggregation kernels the paper's PyTorch integration carries (arXiv
  * 2207.00257, Sec. V-B); it has normalize's shape (Fig. 1): a row-invariant
  * pair is reduced once per row, then every element is mapped. For every CSR
@@ -414,8 +414,8 @@ typedef struct {
   int32_t accum;             /* nrm_accum */
   int32_t hold_outputs;      /* 1: outputs (and their budget) stay until nrm_server_release */
   int32_t use_batch_params;  /* 1: use batch_params for the slots, else the library defaults */
-  int32_t single_plain;      /* 1: a group of one request runs the plain path (two kernels
-                                instead of the batched four); its bits then match the plain
+  int32_t single_plain;      /* 1: a group of one request runs the plain path (one or two
+                                launches over this row only); its bits then match the plain
                                 path rather than the batched one, both within the error bound */
   int32_t spread;            /* 1: waiting requests are spread over the free slots, each free slot
                                 taking ceil(waiting / free slots) of them in arrival order, so that
