@@ -35,6 +35,7 @@ struct BatchHeader {
   const RowDesc* table;    // TABLE: the row table (pinned host memory)
   float* lse;              // softmax: each row's log-sum-exp (device), or NULL
   int64_t run_max;         // rows of wave_max < n <= run_max are run by a block of batch_rows_kernel
+  int64_t grid_x;          // blocks of batch_rows_kernel in one row of its grid
 };
 
 // Device error bits (OR-ed by the kernels, read by nrm_get_device_error).
@@ -127,6 +128,15 @@ constexpr int ROWS_BLOCK = 512;
 constexpr int ROWS_WAVES = ROWS_BLOCK / 64;
 constexpr int ROWS_MAX = 4 * ROWS_WAVES;
 
+// Its grid, for `blocks` blocks: one row of them, or rows of at most
+// ROWS_GRID_X, since a launch's extent in threads is a 32-bit number in each
+// dimension (2^23 blocks of 512 are one too many) and a batch may have up to
+// 2^31 - 1 rows. Block (x, y) is number y * x_extent + x; the few numbers past
+// the last block find no rows.
+constexpr int64_t ROWS_GRID_X = int64_t(1) << 20;
+inline int64_t rows_grid_y(int64_t blocks) { return (blocks + ROWS_GRID_X - 1) / ROWS_GRID_X; }
+inline int64_t rows_grid_x(int64_t blocks) { return (blocks + rows_grid_y(blocks) - 1) / rows_grid_y(blocks); }
+
 // Elements of one resident segment: 512 threads x 8 vectors of 4 binary32
 // (4 vectors of 8 for 2-byte inputs); two blocks fit a CU's registers.
 constexpr int RES_LOG2 = 14;
@@ -138,7 +148,8 @@ constexpr int64_t WAVE_MAX_ELEMS = 2048;
 
 struct BatchPlan {
   int acc;
-  int64_t rows_grid;  // blocks of batch_rows_kernel
+  int64_t rows_grid;    // blocks of batch_rows_kernel in x
+  int64_t rows_grid_y;  // and rows of them
   bool lists;         // rows may be listed: launch the lists' kernels
   int64_t res_grid;   // persistent blocks of the resident rows' kernel
   // resident rows off: the three list kernels' shapes

@@ -974,7 +974,8 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int64_t nrows = h.nrows;
   const int R = h.rows_per_block;
-  if (blockIdx.x == 0 && t == 0) {
+  const int64_t block = (int64_t)blockIdx.y * h.grid_x + blockIdx.x;
+  if (block == 0 && t == 0) {
     const int64_t blocks = (nrows + R - 1) / R;
     a.cnt[CNT_CALL_RUN] = a.cnt[CNT_CALL] + 1;
     a.cnt[CNT_TAKEN] = 0;
@@ -983,7 +984,7 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
     if (nrows < 0 || nrows > a.cap_rows) atomicOr(a.error, NRM_DEVERR_CAPACITY);
   }
   if (nrows < 0 || nrows > a.cap_rows) return;
-  const int64_t r0 = (int64_t)blockIdx.x * R;
+  const int64_t r0 = block * R;
   if (r0 >= nrows) return;
   const int here = nrows - r0 < R ? (int)(nrows - r0) : R;     // the block's rows
   const int rw = R > ROWS_WAVES ? ROWS_MAX / ROWS_WAVES : 1;   // rows per wavefront
@@ -1040,7 +1041,7 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
                                       __HIP_MEMORY_SCOPE_AGENT);
         s_base_tiles = (int64_t)bt;
         s_base_shorts = (int64_t)bs;
-        if (blockIdx.x < ORDERED_BLOCKS) a.block_shorts[blockIdx.x] = BlockShorts{(int64_t)bs, (int64_t)is};
+        if (block < ORDERED_BLOCKS) a.block_shorts[block] = BlockShorts{(int64_t)bs, (int64_t)is};
       }
     }
     lds_barrier();
@@ -1071,8 +1072,8 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
         }
       }
     }
-  } else if (t == 0 && blockIdx.x < ORDERED_BLOCKS) {
-    a.block_shorts[blockIdx.x] = BlockShorts{0, 0};
+  } else if (t == 0 && block < ORDERED_BLOCKS) {
+    a.block_shorts[block] = BlockShorts{0, 0};
   }
   for (uint32_t m = kept & ~list; m; m &= m - 1) {
     const int j = __builtin_ctz(m);
@@ -1084,7 +1085,8 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
 
 template <int ACC>
 hipError_t launch_lists(const BatchPlan& p, const BatchArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((batch_rows_kernel<ACC>), dim3((unsigned)p.rows_grid), dim3(ROWS_BLOCK), 0, s, a);
+  hipLaunchKernelGGL((batch_rows_kernel<ACC>), dim3((unsigned)p.rows_grid, (unsigned)p.rows_grid_y), dim3(ROWS_BLOCK), 0,
+                     s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !p.lists) return e;
   if (a.res_on) {

@@ -250,7 +250,8 @@ BatchPlan plan_of(const nrm_ctx* c, const BatchHeader& h, int64_t rows, int64_t 
   const nrm_batch_params& q = c->bparams;
   BatchPlan p;
   p.acc = acc;
-  p.rows_grid = ceil_div(rows, h.rows_per_block);
+  p.rows_grid = h.grid_x;
+  p.rows_grid_y = nrm::rows_grid_y(ceil_div(rows, h.rows_per_block));
   // no row can be longer than those run on the spot: nothing is listed
   p.lists = longest > std::max<int64_t>(h.run_max, q.wave_max);
   // no more blocks than a small batch can list entries: a listed row of more
@@ -299,7 +300,7 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
   hipKernelNodeParams k;
   std::memset(&k, 0, sizeof(k));
   k.func = const_cast<void*>(nrm::rows_kernel(p.acc));
-  k.gridDim = dim3((unsigned)p.rows_grid);
+  k.gridDim = dim3((unsigned)p.rows_grid, (unsigned)p.rows_grid_y);
   k.blockDim = dim3(nrm::ROWS_BLOCK);
   k.kernelParams = args;
   return hipGraphExecKernelNodeSetParams(g.exec, g.rows, &k);
@@ -328,6 +329,7 @@ void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeade
   } else {
     h->rows_per_block = mean >= 4096 ? 2 : mean >= 1536 ? 4 : mean > 512 || rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
   }
+  h->grid_x = nrm::rows_grid_x(ceil_div(rows, h->rows_per_block));
 }
 
 // Run the launch sequence on `s` for a batch of at most `elems` elements whose

@@ -1,0 +1,131 @@
+// CPU tests of the batched path's host code (paper_2207_00257_amd/csrc/
+// nrm_batched_api.cpp, included below so that its file-local rules can be
+// called): a HIP runtime over host memory, and a launch that records what it
+// is given, stand in for the GPU. Built with g++ and run, one test per process,
+// by tests/test_batched_host_cpu.py. Exit status 0: passed.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <functional>
+#include <map>
+#include <string>
+
+#include "nrm_batched_api.cpp"
+
+static int g_failures = 0;
+#define CHECK(cond)                                                          \
+  do {                                                                       \
+    if (!(cond)) {                                                           \
+      fprintf(stderr, "%s:%d: CHECK failed: %s\n", __FILE__, __LINE__, #cond); \
+      ++g_failures;                                                          \
+    }                                                                        \
+  } while (0)
+
+// ---- the stand-ins -----------------------------------------------------------------
+
+static BatchPlan g_plan;   // what the last launch was given
+static BatchArgs g_args;
+static int g_launches = 0;
+static std::function<hipError_t(const BatchPlan&, const BatchArgs&)> g_launch;
+
+namespace nrm {
+std::string& last_error() {
+  static std::string text;
+  return text;
+}
+int default_ctx(nrm_ctx**) { return NRM_EINVAL; }
+const void* rows_kernel(int) { return nullptr; }
+hipError_t launch_batch(const BatchPlan& p, const BatchArgs& a, hipStream_t) {
+  g_plan = p;
+  g_args = a;
+  ++g_launches;
+  return g_launch ? g_launch(p, a) : hipSuccess;
+}
+}  // namespace nrm
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) { return (*p = malloc(n)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void* p) { return hipFree(p); }
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = reinterpret_cast<hipEvent_t>(1); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = nullptr; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+// no graph can be made here: tests use batches that are launched directly
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t*) { return hipErrorNotSupported; }
+hipError_t hipGraphGetRootNodes(hipGraph_t, hipGraphNode_t*, size_t*) { return hipErrorNotSupported; }
+hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, char*, size_t) { return hipErrorNotSupported; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t hipGraphExecKernelNodeSetParams(hipGraphExec_t, hipGraphNode_t, const hipKernelNodeParams*) {
+  return hipErrorNotSupported;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+}
+
+struct Ctx : nrm_ctx {
+  Ctx() { bparams = default_batch_params(); }
+  ~Ctx() { nrm::batch_free(this); }
+};
+
+// ---- tests -------------------------------------------------------------------------
+
+// Whatever a batch has rows and elements, its first launch is one that the
+// hardware takes (fewer than 2^32 threads in each dimension) and that has a
+// block for every row.
+static void test_rows_grid() {
+  Ctx c;
+  for (int segments : {64, 0}) {
+    c.bparams.resident_segments = segments;
+    for (int64_t rows : {int64_t(1), int64_t(512), int64_t(513), int64_t(5000), (int64_t(1) << 20) - 1, int64_t(1) << 21,
+                         (int64_t(1) << 21) + 1, (int64_t(1) << 24) + 7, int64_t(1) << 25, int64_t(1) << 28,
+                         (int64_t(1) << 28) + 1, int64_t(INT32_MAX)})
+      for (int64_t mean : {0, 1, 17, 256, 600, 2048, 4096, 20000, 1 << 21}) {
+        const int64_t elems = rows * mean;
+        BatchHeader h;
+        memset(&h, 0, sizeof(h));
+        h.nrows = rows;
+        cut_rows(c.bparams, rows, elems, &h);
+        const BatchPlan p = plan_of(&c, h, rows, elems, elems, NRM_ACC_F32);
+        CHECK(p.rows_grid >= 1 && p.rows_grid * nrm::ROWS_BLOCK < int64_t(1) << 32);
+        CHECK(p.rows_grid_y >= 1 && p.rows_grid_y <= 65535);
+        CHECK(h.grid_x == p.rows_grid);
+        CHECK(p.rows_grid * p.rows_grid_y * h.rows_per_block >= rows);
+        CHECK((p.rows_grid * p.rows_grid_y - p.rows_grid_y) * h.rows_per_block < rows);  // hardly any without rows
+        CHECK(p.res_grid >= 1 && p.res_grid <= c.bparams.resident_grid);
+      }
+  }
+}
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> tests = {
+      {"rows_grid", test_rows_grid},
+  };
+  const auto t = tests.find(argc > 1 ? argv[1] : "");
+  if (t == tests.end()) {
+    fprintf(stderr, "no such test\n");
+    return 2;
+  }
+  t->second();
+  if (g_failures) {
+    fprintf(stderr, "%d check(s) failed\n", g_failures);
+    return 1;
+  }
+  printf("%s: passed\n", argv[1]);
+  return 0;
+}
