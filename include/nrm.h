@@ -364,7 +364,9 @@ int nrm_softmax_batched(nrm_ctx* ctx, float* out, const float* in, const int64_t
  * place; rows may mix dtypes. Rows are validated on the host. The context
  * keeps four such staging buffers and uses them in turn (a CSR call that
  * replays a graph uses them too): a call blocks the host only while the call
- * four before it on the same context has not finished. */
+ * four before it on the same context has not finished. On a capturing stream
+ * the launches become nodes of the caller's graph, and the table gets pinned
+ * memory of its own, held until the context is destroyed. */
 int nrm_normalize_rows(nrm_ctx* ctx, const nrm_row* rows, int64_t nrows, int accum, void* stream);
 
 /* Reserve batched workspace for up to max_rows rows and max_elems elements

@@ -332,6 +332,28 @@ void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeade
   h->grid_x = nrm::rows_grid_x(ceil_div(rows, h->rows_per_block));
 }
 
+// A row table of its own for a call that a caller's graph captures: the
+// replays read it in place, whatever later calls stage. Held until the context
+// is destroyed.
+int keep_table(BatchWorkspace& w, const nrm_row* table, int64_t nrows, const RowDesc** dev) {
+  const size_t bytes = sizeof(RowDesc) * (size_t)nrows;
+  void *host = nullptr, *view = nullptr;
+  // allocating is not a stream operation: allowed beside any kind of capture
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return hip_fail(e, "hipThreadExchangeStreamCaptureMode");
+  e = hipHostMalloc(&host, bytes, hipHostMallocCoherent | hipHostMallocMapped);
+  const hipError_t e2 = hipThreadExchangeStreamCaptureMode(&mode);  // the caller's again
+  if (e != hipSuccess) return fail(NRM_ENOMEM, std::string("pinned row table hipHostMalloc: ") + hipGetErrorString(e));
+  w.captured.push_back(host);
+  if (e2 != hipSuccess) return hip_fail(e2, "hipThreadExchangeStreamCaptureMode");
+  e = hipHostGetDevicePointer(&view, host, 0);
+  if (e != hipSuccess) return hip_fail(e, "hipHostGetDevicePointer");
+  std::memcpy(host, table, bytes);
+  *dev = static_cast<const RowDesc*>(view);
+  return NRM_OK;
+}
+
 // Run the launch sequence on `s` for a batch of at most `elems` elements whose
 // longest row has at most `longest`. A row table is staged in the next ring
 // buffer first.
@@ -343,15 +365,32 @@ int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nr
   a.header = h;
   cut_rows(c->bparams, nrows, elems, &a.header);
   BatchPlan p = plan_of(c, a.header, nrows, elems, longest, acc);
-  const bool replay = c->bparams.graph && elems >= kGraphElems;
-  const bool ring = replay || table;
+  bool replay = c->bparams.graph && elems >= kGraphElems;
+  bool ring = replay || table;
+  if (ring) {
+    hipStreamCaptureStatus state = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &state) != hipSuccess) {
+      // (the null stream beside a capture on a blocking one): the launch says so
+      (void)hipGetLastError();
+      state = hipStreamCaptureStatusNone;
+    }
+    if (state != hipStreamCaptureStatusNone) {
+      // the launches themselves go into the caller's graph (a graph launched
+      // on a capturing stream leaves it empty)
+      replay = ring = false;
+      if (table) {
+        int st = keep_table(w, table, nrows, &a.header.table);
+        if (st != NRM_OK) return st;
+      }
+    }
+  }
   const int buf = w.next;
   if (ring && w.staged_pending[buf]) {  // the call that used this buffer or graph before must be done with it
     e = hipEventSynchronize(w.staged[buf]);
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
     w.staged_pending[buf] = false;
   }
-  if (table) {
+  if (ring && table) {
     std::memcpy(static_cast<char*>(w.host) + w.staging * buf, table, sizeof(RowDesc) * (size_t)nrows);
     a.header.table = w.table[buf];
   }
@@ -402,6 +441,7 @@ void batch_free(nrm_ctx* c) {
   for (hipEvent_t ev : w.events) (void)hipEventDestroy(ev);
   if (w.dev) (void)hipFree(w.dev);
   if (w.host) (void)hipHostFree(w.host);
+  for (void* p : w.captured) (void)hipHostFree(p);
   w = BatchWorkspace();
 }
 }  // namespace nrm

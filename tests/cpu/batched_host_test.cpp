@@ -10,6 +10,8 @@
 #include <functional>
 #include <map>
 #include <string>
+#include <utility>
+#include <vector>
 
 #include "nrm_batched_api.cpp"
 
@@ -27,6 +29,7 @@ static int g_failures = 0;
 static BatchPlan g_plan;   // what the last launch was given
 static BatchArgs g_args;
 static int g_launches = 0;
+static bool g_capturing = false;
 static std::function<hipError_t(const BatchPlan&, const BatchArgs&)> g_launch;
 
 namespace nrm {
@@ -55,6 +58,7 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { memcpy(d
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "error"; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
@@ -65,6 +69,15 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = nullptr; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
+  static hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
+  std::swap(mode, *m);
+  return hipSuccess;
+}
 // no graph can be made here: tests use batches that are launched directly
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t*) { return hipErrorNotSupported; }
@@ -112,9 +125,51 @@ static void test_rows_grid() {
   }
 }
 
+// A captured call's replays see its own row table, whatever was staged since,
+// and a large batch on a capturing stream is launched, not replayed.
+static void test_captured_tables() {
+  Ctx c;
+  std::vector<float> in(100000), out(100000);
+  auto call = [&](int64_t first, int64_t n) {
+    std::vector<nrm_row> rows(3);
+    for (int64_t k = 0; k < 3; ++k) {
+      rows[k].in = in.data() + first + k * n;
+      rows[k].out = out.data() + first + k * n;
+      rows[k].n = n;
+      rows[k].in_dtype = rows[k].out_dtype = NRM_F32;
+    }
+    CHECK(nrm_normalize_rows(&c, rows.data(), 3, NRM_ACC_F32, nullptr) == NRM_OK);
+    CHECK(g_args.header.table[2].n == n);
+    return g_args.header.table;
+  };
+  call(0, 5);
+  g_capturing = true;
+  std::vector<const RowDesc*> captured;
+  for (int k = 0; k < 6; ++k) captured.push_back(call(100 * k, 10 + k));
+  g_capturing = false;
+  for (int k = 0; k < 9; ++k) call(50000, 1000 + k);
+  CHECK(nrm_batch_reserve(&c, 1 << 16, 1 << 20) == NRM_OK);
+  call(50000, 7);
+  for (int k = 0; k < 6; ++k)
+    for (int r = 0; r < 3; ++r) {
+      CHECK(captured[k][r].n == 10 + k);
+      CHECK(captured[k][r].in == reinterpret_cast<const char*>(in.data() + 100 * k + r * (10 + k)));
+    }
+  const int launches = g_launches;
+  const int64_t offsets[2] = {0, 10};
+  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets, 1, kGraphElems, NRM_ACC_F32,
+                                 nullptr) != NRM_OK);  // a replay: no graph can be made here
+  g_capturing = true;
+  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets, 1, kGraphElems, NRM_ACC_F32,
+                                 nullptr) == NRM_OK);
+  g_capturing = false;
+  CHECK(g_launches == launches + 1 && g_args.header.offsets == offsets);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"rows_grid", test_rows_grid},
+      {"captured_tables", test_captured_tables},
   };
   const auto t = tests.find(argc > 1 ? argv[1] : "");
   if (t == tests.end()) {
