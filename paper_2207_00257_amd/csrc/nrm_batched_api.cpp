@@ -211,6 +211,7 @@ int reserve(nrm_ctx* c, int64_t rows, int64_t items) {
   a.cap_items = cap_items;
   w.cap_rows = cap_rows;
   w.cap_items = cap_items;
+  w.dirty = false;
   for (bool& p : w.staged_pending) p = false;
   // the call's words and counters, the tags, totals and arrival counts
   e = hipMemset(d + L.small, 0, L.total - L.small);
@@ -332,6 +333,18 @@ void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeade
   h->grid_x = nrm::rows_grid_x(ceil_div(rows, h->rows_per_block));
 }
 
+// After a failed launch: the rows' kernel may have run without the launches
+// that take its lists' entries and zero the counters, and the next call would
+// append behind entries that point at the failed call's arrays.
+int empty_lists(BatchWorkspace& w) {
+  hipError_t e = hipDeviceSynchronize();
+  if (e == hipSuccess)
+    e = hipMemset(w.args.cnt + nrm::CNT_SET0, 0, sizeof(int64_t) * (nrm::CNT_COUNT - nrm::CNT_SET0));
+  if (e != hipSuccess) return hip_fail(e, "emptying the work lists after a failed launch");
+  w.dirty = false;
+  return NRM_OK;
+}
+
 // A row table of its own for a call that a caller's graph captures: the
 // replays read it in place, whatever later calls stage. Held until the context
 // is destroyed.
@@ -361,6 +374,10 @@ int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nr
               int acc, hipStream_t s) {
   BatchWorkspace& w = c->batch;
   hipError_t e;
+  if (w.dirty) {
+    int st = empty_lists(w);
+    if (st != NRM_OK) return st;
+  }
   BatchArgs a = args_of(c);
   a.header = h;
   cut_rows(c->bparams, nrows, elems, &a.header);
@@ -412,10 +429,12 @@ int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nr
     e = set_rows_node(g, p, a);
     if (e != hipSuccess) return hip_fail(e, "hipGraphExecKernelNodeSetParams");
     e = hipGraphLaunch(g.exec, s);
-    if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
   } else {
     e = nrm::launch_batch(p, a, s);
-    if (e != hipSuccess) return hip_fail(e, "batched kernel launch");
+  }
+  if (e != hipSuccess) {
+    w.dirty = true;
+    return hip_fail(e, replay ? "hipGraphLaunch" : "batched kernel launch");
   }
   if (ev) (void)hipEventRecord(ev[1], s);
   if (ring) {

@@ -68,6 +68,7 @@ struct BatchWorkspace {
   int next = 0;                // the buffer (and graph) the next call uses
   hipEvent_t staged[kStagingRing] = {};  // recorded after the call that used the buffer
   bool staged_pending[kStagingRing] = {};
+  bool dirty = false;          // a launch failed: the work lists may hold entries that no launch took
   std::vector<void*> captured;  // pinned row tables of calls captured in a caller's graph
   // captured launch sequences: per reduction kind (plain, compensated,
   // softmax) and staging buffer (one is not changed while its last replay runs)

@@ -166,10 +166,43 @@ static void test_captured_tables() {
   CHECK(g_launches == launches + 1 && g_args.header.offsets == offsets);
 }
 
+// A call whose later launches fail leaves its list entries behind: the next
+// call finds the lists empty.
+static void test_failed_launch() {
+  Ctx c;
+  std::vector<float> in(1 << 16);
+  const int64_t offsets[2] = {0, 1 << 16};
+  auto call = [&] {
+    return nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets, 1, 1 << 16, NRM_ACC_F32, nullptr);
+  };
+  auto listed = [](const BatchArgs& a) {
+    int64_t n = 0;
+    for (int set = 0; set < 2; ++set)
+      for (int k = 0; k < nrm::LIST_COUNTERS; ++k) n += a.cnt[nrm::CNT_SET0 + set * nrm::CNT_SET_STRIDE + k * nrm::CNT_LINE];
+    return n;
+  };
+  CHECK(call() == NRM_OK);
+  for (int set = 0; set < 2; ++set) {
+    g_launch = [&](const BatchPlan&, const BatchArgs& a) {
+      CHECK(listed(a) == 0);
+      for (int k = 0; k < nrm::LIST_COUNTERS; ++k) a.cnt[nrm::CNT_SET0 + set * nrm::CNT_SET_STRIDE + k * nrm::CNT_LINE] = 4;
+      return hipErrorLaunchFailure;
+    };
+    CHECK(call() == NRM_EHIP);
+  }
+  g_launch = [&](const BatchPlan&, const BatchArgs& a) {
+    CHECK(listed(a) == 0);
+    return hipSuccess;
+  };
+  CHECK(call() == NRM_OK);
+  g_launch = nullptr;
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"rows_grid", test_rows_grid},
       {"captured_tables", test_captured_tables},
+      {"failed_launch", test_failed_launch},
   };
   const auto t = tests.find(argc > 1 ? argv[1] : "");
   if (t == tests.end()) {

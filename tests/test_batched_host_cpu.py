@@ -1,7 +1,8 @@
 """The batched path's host code on the CPU (paper_2207_00257_amd/csrc/
 nrm_batched_api.cpp) with a HIP runtime over host memory in place of the GPU's
 (tests/cpu/batched_host_test.cpp): the launches' shapes over
-all row counts, the row tables of captured calls.
+all row counts, the row tables of captured calls, the work lists after
+a failed launch.
 Built with g++ only, under AddressSanitizer and UndefinedBehaviorSanitizer."""
 import os
 import subprocess
@@ -25,7 +26,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["rows_grid", "captured_tables"])
+@pytest.mark.parametrize("case", ["rows_grid", "captured_tables", "failed_launch"])
 def test_batched_host(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
