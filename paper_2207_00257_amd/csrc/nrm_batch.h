@@ -112,14 +112,18 @@ struct BatchArgs {
   int res_on;
   // by a row's first entry: its entries' partials (two tagged words each),
   // its total (two tagged words), and the count of its published partials (0
-  // between calls); without resident rows tile_tagged and tile_total hold
-  // plain partials and results
+  // between calls)
   unsigned long long* tagged;       // [2 * cap_items], shorts
   unsigned long long* rowtot;       // [2 * cap_items]
   unsigned* arrivals;               // [cap_items]
   unsigned long long* tile_tagged;  // [2 * cap_items], tiles
   unsigned long long* tile_total;   // [2 * cap_items]
   unsigned* tile_arrivals;          // [cap_items]
+  // without resident rows: each tile's partial, and by a row's first tile its
+  // result, plain (apart from the tagged words, of which any bits that equal a
+  // call's tag count as published)
+  void* partials;    // [cap_items] x 8 bytes
+  RowRes* results;   // [cap_items]
 };
 
 // batch_rows_kernel: blocks of ROWS_BLOCK threads, at most ROWS_MAX rows each

@@ -633,7 +633,7 @@ __global__ void __launch_bounds__(1024) batch_phase1_kernel(BatchArgs a) {
   const int64_t n_items = n_long + n_short;
   const int64_t keep_item = n_long - a.keep_tiles;
   float* lse = lse_out(a);
-  Acc<ACC>* part = reinterpret_cast<Acc<ACC>*>(a.tile_tagged);
+  Acc<ACC>* part = static_cast<Acc<ACC>*>(a.partials);
   for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
     const Item it = uniform_item(item < n_long ? a.tiles[item] : a.shorts[item - n_long]);
     if (it.row < 0) continue;
@@ -663,7 +663,7 @@ __global__ void __launch_bounds__(1024) batch_rowsum_kernel(BatchArgs a) {
   const int64_t* lists = list_counters(a, a.cnt[CNT_CALL_RUN]);
   const int64_t n_lrows = lists[LIST_LONG_ROWS * CNT_LINE];
   float* lse = lse_out(a);
-  const Acc<ACC>* part = reinterpret_cast<const Acc<ACC>*>(a.tile_tagged);
+  const Acc<ACC>* part = static_cast<const Acc<ACC>*>(a.partials);
   for (int64_t k = blockIdx.x; k < n_lrows; k += gridDim.x) {
     const int64_t first = a.lrow_first[k];
     const int32_t row = a.tiles[first].row;
@@ -671,7 +671,7 @@ __global__ void __launch_bounds__(1024) batch_rowsum_kernel(BatchArgs a) {
     Acc<ACC> tot = combine_partials<ACC>(part + first, count, tree, tiles);
     if (threadIdx.x == 0) {
       const RowMap<ACC> f = RowMap<ACC>::of(tot);
-      reinterpret_cast<RowRes*>(a.tile_total)[first] = f.result();
+      a.results[first] = f.result();
       if constexpr (ACC == ACC_SOFTMAX) {
         if (lse) lse[row] = f.lse();
       }
@@ -692,7 +692,7 @@ __global__ void __launch_bounds__(1024) batch_phase2_kernel(BatchArgs a) {
     const RowDesc& d = it.d;
     const int64_t b = (int64_t)it.tile << a.tile_log2;
     const int64_t e = b + a.tile < d.n ? b + a.tile : d.n;
-    dispatch_tile_map<ACC, U>(d, b, e, RowMap<ACC>::of(reinterpret_cast<const RowRes*>(a.tile_total)[pos - it.tile]));
+    dispatch_tile_map<ACC, U>(d, b, e, RowMap<ACC>::of(a.results[pos - it.tile]));
   }
 }
 

@@ -118,7 +118,7 @@ void destroy_graph(BatchWorkspace& w) {
 
 // Layout of the single device allocation.
 struct Layout {
-  size_t tiles, shorts, block_shorts, lrow_first, small, tagged, rowtot, arrivals, tile_tagged, tile_total,
+  size_t tiles, shorts, block_shorts, lrow_first, partials, results, small, tagged, rowtot, arrivals, tile_tagged, tile_total,
       tile_arrivals, total;
 };
 
@@ -134,6 +134,8 @@ Layout layout_for(int64_t cap_rows, int64_t cap_items) {
   L.shorts = take(sizeof(nrm::Item) * cap_items);
   L.block_shorts = take(sizeof(nrm::BlockShorts) * nrm::ORDERED_BLOCKS);
   L.lrow_first = take(sizeof(int64_t) * cap_rows);
+  L.partials = take(8 * cap_items);
+  L.results = take(sizeof(nrm::RowRes) * cap_items);
   // zeroed from here on
   L.small = take(kSmallBytes);
   L.tagged = take(16 * cap_items);
@@ -199,6 +201,8 @@ int reserve(nrm_ctx* c, int64_t rows, int64_t items) {
   a.shorts = reinterpret_cast<nrm::Item*>(d + L.shorts);
   a.block_shorts = reinterpret_cast<nrm::BlockShorts*>(d + L.block_shorts);
   a.lrow_first = reinterpret_cast<int64_t*>(d + L.lrow_first);
+  a.partials = d + L.partials;
+  a.results = reinterpret_cast<nrm::RowRes*>(d + L.results);
   a.cnt = reinterpret_cast<int64_t*>(d + L.small);
   a.error = reinterpret_cast<int*>(d + L.small + kErrorOffset);
   a.tagged = reinterpret_cast<unsigned long long*>(d + L.tagged);

@@ -198,11 +198,49 @@ static void test_failed_launch() {
   g_launch = nullptr;
 }
 
+// No array of the workspace reaches into another. The tagged words are then
+// written by publishing alone: plain floats among them (the partials and results
+// of calls without resident rows) could pass for a later call's.
+static void test_workspace_layout() {
+  Ctx c;
+  for (int64_t rows : {1, 1000, 70000}) {
+    CHECK(nrm_batch_reserve(&c, rows, rows * 100000) == NRM_OK);
+    const BatchArgs& a = c.batch.args;
+    const size_t n = (size_t)a.cap_items;
+    const struct {
+      const void* at;
+      size_t bytes;
+    } arrays[] = {{a.tiles, sizeof(nrm::Item) * n},
+                  {a.shorts, sizeof(nrm::Item) * n},
+                  {a.block_shorts, sizeof(nrm::BlockShorts) * nrm::ORDERED_BLOCKS},
+                  {a.lrow_first, sizeof(int64_t) * (size_t)a.cap_rows},
+                  {a.cnt, sizeof(int64_t) * nrm::CNT_COUNT},
+                  {a.error, sizeof(int)},
+                  {a.partials, 8 * n},
+                  {a.results, sizeof(nrm::RowRes) * n},
+                  {a.tagged, 16 * n},
+                  {a.rowtot, 16 * n},
+                  {a.arrivals, 4 * n},
+                  {a.tile_tagged, 16 * n},
+                  {a.tile_total, 16 * n},
+                  {a.tile_arrivals, 4 * n}};
+    const size_t total = layout_for(a.cap_rows, a.cap_items).total;
+    for (const auto& x : arrays) {
+      CHECK((const char*)x.at >= (const char*)c.batch.dev && (const char*)x.at + x.bytes <= (const char*)c.batch.dev + total);
+      for (const auto& y : arrays)
+        CHECK(&x == &y || (const char*)x.at + x.bytes <= (const char*)y.at || (const char*)y.at + y.bytes <= (const char*)x.at);
+    }
+    for (const unsigned long long* tagged : {a.tagged, a.rowtot, a.tile_tagged, a.tile_total})
+      for (size_t k = 0; k < 2 * n; ++k) CHECK(tagged[k] == 0);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"rows_grid", test_rows_grid},
       {"captured_tables", test_captured_tables},
       {"failed_launch", test_failed_launch},
+      {"workspace_layout", test_workspace_layout},
   };
   const auto t = tests.find(argc > 1 ? argv[1] : "");
   if (t == tests.end()) {
