@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "nrm.h"
+#include "nrm_internal.h"
 
 namespace nrm {
 
@@ -146,6 +147,28 @@ inline int64_t rows_grid_x(int64_t blocks) { return (blocks + rows_grid_y(blocks
 constexpr int RES_LOG2 = 14;
 constexpr int RES_BLOCK = 512;
 constexpr int RES_MAX_SEGMENTS = 64;  // one wavefront lane per segment in the merge
+
+// Long rows' tile sums beside the resident rows: vectors per thread per
+// iteration, chains per thread, and the elements of a part. A longer tile is
+// summed part by part, so that its threads' chains, and with them the row's
+// summation tree, stay low.
+constexpr int TILE_U = 4;
+constexpr int TILE_NA = 8;
+constexpr int64_t TILE_PART = int64_t(1) << 19;
+
+// Height of such a row's summation tree (binary32 sums): a thread's part
+// (CHAIN_ADDS + 1 additions in a chain, the merge of its chains, one addition
+// per CHAIN_ADDS elements of every chain), the block's (wavefront 6, its
+// wavefronts 3), the tile's parts one after the other, and the row's tiles (RES_BLOCK at a
+// time by a block, then up to MAX_ROW_TILES / RES_BLOCK totals by a wavefront,
+// two per lane). The published bound is gamma_62.
+constexpr int log2_of(int64_t x) { return x <= 1 ? 0 : 1 + log2_of(x / 2); }
+constexpr int long_row_height(int tile_log2) {
+  const int64_t tile = int64_t(1) << tile_log2, part = tile < TILE_PART ? tile : TILE_PART;
+  const int64_t flush = (int64_t)RES_BLOCK * CHAIN_ADDS * TILE_NA;
+  return (int)(CHAIN_ADDS + 1 + log2_of(TILE_NA) + (part + flush - 1) / flush + log2_of(RES_BLOCK) + (tile / part - 1) +
+               log2_of(RES_BLOCK) + log2_of(MAX_ROW_TILES / RES_BLOCK));
+}
 
 // The longest row of one wavefront (2048 binary32: eight 16-byte vectors per lane).
 constexpr int64_t WAVE_MAX_ELEMS = 2048;

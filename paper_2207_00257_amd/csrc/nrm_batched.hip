@@ -419,14 +419,7 @@ __device__ __forceinline__ void dispatch_tile_map(const RowDesc& d, int64_t b, i
 
 // ---- the long rows' tiles and the resident rows, persistently -------------------------------
 
-constexpr int TILE_U = 4;      // tile sums: vectors per thread per iteration
-constexpr int TILE_NA = 8;     // and chains
-constexpr int TILE_MAP_U = 4;  // tile divides
-// A tile is summed in parts of at most this many elements: a thread's tree
-// then has height 36 (16 + 1 additions in a chain, 3 merges of its 8 chains,
-// 16 of its totals), the whole row's 36 + 9 (wavefront, block) + 16
-// (gather_tiles), and up to 4 more for tiles of several parts.
-constexpr int64_t TILE_PART = int64_t(1) << 20;
+constexpr int TILE_MAP_U = 4;  // tile divides: vectors per thread per iteration
 // elements of one unit of the divide: one block-iteration of 4-byte elements
 constexpr int64_t MAP_UNIT = (int64_t)RES_BLOCK * TILE_MAP_U * 4;
 
@@ -437,6 +430,7 @@ constexpr int64_t MAP_UNIT = (int64_t)RES_BLOCK * TILE_MAP_U * 4;
 // Every thread must call it; the result is valid in thread 0.
 constexpr int TILE_ROUNDS = (int)(MAX_ROW_TILES / RES_BLOCK);
 static_assert(TILE_ROUNDS <= 128, "two rounds' totals per lane");
+static_assert(long_row_height(22) <= 62, "the published bound");
 template <int ACC>
 __device__ __forceinline__ Acc<ACC> gather_tiles(const ResExchange& x, int64_t count, Acc<ACC>* slots,
                                                  Acc<ACC>* rounds) {

@@ -235,12 +235,30 @@ static void test_workspace_layout() {
   }
 }
 
+// The published error bound is that of a summation tree of height 62, for every
+// tile size that the parameters take.
+static void test_tree_height() {
+  Ctx c;
+  for (int t = 10; t <= 22; ++t) {
+    nrm_batch_params p = c.bparams;
+    p.tile_log2 = t;
+    CHECK(t >= 18 || check_batch_params(p) == NRM_OK);
+    CHECK(nrm::long_row_height(t) <= 62);
+  }
+  nrm_batch_params p = c.bparams;
+  p.tile_log2 = 22;
+  p.block = 1024;
+  p.unroll = 8;
+  CHECK(check_batch_params(p) == NRM_OK);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"rows_grid", test_rows_grid},
       {"captured_tables", test_captured_tables},
       {"failed_launch", test_failed_launch},
       {"workspace_layout", test_workspace_layout},
+      {"tree_height", test_tree_height},
   };
   const auto t = tests.find(argc > 1 ? argv[1] : "");
   if (t == tests.end()) {

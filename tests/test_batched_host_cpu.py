@@ -2,7 +2,7 @@
 nrm_batched_api.cpp) with a HIP runtime over host memory in place of the GPU's
 (tests/cpu/batched_host_test.cpp): the launches' shapes over
 all row counts, the row tables of captured calls, the work lists after
-a failed launch, the workspace's arrays.
+a failed launch, the workspace's arrays, the summation tree's height.
 Built with g++ only, under AddressSanitizer and UndefinedBehaviorSanitizer."""
 import os
 import subprocess
@@ -26,7 +26,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["rows_grid", "captured_tables", "failed_launch", "workspace_layout"])
+@pytest.mark.parametrize("case", ["rows_grid", "captured_tables", "failed_launch", "workspace_layout", "tree_height"])
 def test_batched_host(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
