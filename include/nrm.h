@@ -120,9 +120,9 @@ typedef struct {
   int32_t resident_n;   /* 0..2^20: n in (small_n, resident_n] (compensated: at most 2^19) runs as one
                            launch, each block holding its elements in registers while the blocks
                            exchange their sums: one read, one write, one launch. One block of 256
-                           threads per 2^12 elements up to 2^18, above one of 512 threads per 2^14 (at
-                           most 64 blocks, all of which must be able to run at once); every block
-                           reads every block's sum. Default 2^20; 0: never */
+                           threads per 2^12 elements up to 2^18, above one of 512 threads per 2^14; every
+                           block reads every block's sum, and takes over the elements of blocks that
+                           cannot run. Default 2^20; 0: never */
 } nrm_params;
 
 /* Launch parameters of the ragged batched path. Start from

@@ -89,9 +89,8 @@ int check_params(const nrm_params& p) {
 }
 
 // The context's small workspace: the ticket (0), the sum (128), the device
-// error word (192), the mid-size single-launch form's call number (256),
-// arrival count (264) and stall marker (272), and from 512 its segments'
-// tagged partials (64 x 16 bytes).
+// error word (192), the mid-size single-launch form's call number (256) and
+// arrival count (264), and from 512 its segments' tagged sums (64 x 16 bytes).
 constexpr size_t kSmallWs = 512 + 64 * 16;
 
 std::mutex g_default_mu;
@@ -409,8 +408,7 @@ int nrm_create(nrm_ctx** ctx, int device) {
   c->sum = reinterpret_cast<float*>(sm + 128);
   c->dev_error = reinterpret_cast<int*>(sm + 192);
   c->res = nrm::PlainResidentWs{reinterpret_cast<unsigned long long*>(sm + 512), reinterpret_cast<unsigned*>(sm + 264),
-                                reinterpret_cast<unsigned long long*>(sm + 256),
-                                reinterpret_cast<unsigned long long*>(sm + 272), c->dev_error, c->sum};
+                                reinterpret_cast<unsigned long long*>(sm + 256), c->sum, 0};
   int st = ensure_partials(c, 16384);
   if (st != NRM_OK) {
     (void)hipFree(small);

@@ -562,8 +562,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
                        : dispatch_tile_reduce<ACC, TILE_U, true, TILE_NA>(d, c, ce, slots));
           if (ce < e) lds_barrier();  // slots are reused
         }
-        const ResExchange x{a.tile_tagged + 2 * first, a.tile_total + 2 * first, a.tile_arrivals + first, ep, a.error,
-                            stall, nullptr};
+        const ResExchange x{a.tile_tagged + 2 * first, a.tile_total + 2 * first, a.tile_arrivals + first, ep, a.error, stall};
         const int64_t count = (d.n + a.tile - 1) >> a.tile_log2;
         if (threadIdx.x == 0) {
           publish_tagged<ACC>(x.slots + 2 * it.tile, ep, p);
@@ -584,7 +583,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
       } else {
         // the row's entries are consecutive: its first is at pos - tile
         const int64_t first = pos - it.tile;
-        const ResExchange x{a.tagged + 2 * first, a.rowtot + 2 * first, a.arrivals + first, ep, a.error, stall, nullptr};
+        const ResExchange x{a.tagged + 2 * first, a.rowtot + 2 * first, a.arrivals + first, ep, a.error, stall};
         dispatch_resident<ACC>(d, it.tile, x, slots, &s_bcast, lse ? lse + it.row : nullptr);
       }
     }
@@ -606,8 +605,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
     if (b >= d.n) continue;
     const int64_t e = b + unit < d.n ? b + unit : d.n;
     const int64_t first = pos - it.tile;
-    const ResExchange x{a.tile_tagged + 2 * first, a.tile_total + 2 * first, a.tile_arrivals + first, ep, a.error, stall,
-                        nullptr};
+    const ResExchange x{a.tile_tagged + 2 * first, a.tile_total + 2 * first, a.tile_arrivals + first, ep, a.error, stall};
     lds_barrier();  // s_bcast is reused
     if (threadIdx.x == 0) s_bcast = RowMap<ACC>::of(wait_tagged<ACC>(x, x.total)).result();
     lds_barrier();
@@ -1071,7 +1069,7 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
   }
   for (uint32_t m = kept & ~list; m; m &= m - 1) {
     const int j = __builtin_ctz(m);
-    const ResExchange none{nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
+    const ResExchange none{nullptr, nullptr, nullptr, 0, nullptr, nullptr};
     dispatch_resident<ACC, true>(uniform_desc(s_rows[j]), 0, none, slots, &s_bcast, h.lse ? h.lse + (r0 + j) : nullptr);
     lds_barrier();  // slots and s_bcast are reused
   }
@@ -1132,45 +1130,193 @@ hipError_t small_acc(const RowDesc& d, float* sum_out, hipStream_t s) {
 // ---- the plain path's single-launch form for mid-size n ---------------------------------
 // n in (small_n, 2^20]: one block per segment of the input, at most
 // PRES_MAX_SEGMENTS of them, each held in registers from its read to its write
-// while the blocks exchange their segment sums: every block reads every sum
-// (DIRECT; one lane of a wavefront per segment). Two transfers and one launch
-// instead of three and two. The grid is the row's segments, so every block of
-// the launch must be able to run at once. The call number that tags the
-// partials lives in the workspace; the last block to arrive moves it on (every
-// block read it before arriving), so consecutive calls on one workspace never
-// read each other's partials.
+// while the blocks exchange their segment sums: every block reads every sum,
+// one lane of a wavefront per segment. Two transfers and one launch instead of
+// three and two. The call number that tags the sums lives in the workspace; the
+// last block to arrive moves it on (every block read it before arriving), so
+// consecutive calls on one workspace never read each other's sums.
+//
+// The blocks need not all be able to run at once. A segment belongs to the block
+// that publishes its sum, by a compare-and-swap against the slot's word as it
+// read it meanwhile. A block that has waited PRES_PATIENCE polls takes a segment
+// whose sum is missing, reads it and publishes its sum, waits again, and in the
+// end divides all segments that are its own: one running block alone ends the
+// call. Nothing is written before every sum is published, so a block that starts
+// late, and reads elements already divided in place, finds its slot taken or its
+// swap fails.
 //
 // Launch and exchange latency bound it. A short input takes segments of 2^12
 // elements on 256 threads (more CUs load at once), one of more than
 // PRES_SHORT_MAX segments of 2^14 on 512, which keeps the sums of 2^20
 // elements within one wavefront's lanes and the launch within 64 blocks.
-// Per call back to back, one box: 2^18 binary32 6.1 us either way; 2^19 6.5 us
-// and 2^20 7.2 us against 8.1 and 8.4 us for the two kernels (with 256 segments
-// of 2^12 and the last block publishing the total, 8.6 and 10.9 us). The
-// compensated sum's longer chains lose that from 2^20 on (8.2 against 7.7 us;
-// 2^19: 7.5 and 7.7), so it stops at 2^19.
+// Per call back to back, one box: 2^16 binary32 4.7 us, 2^18 5.2, 2^19 6.3, 2^20 6.9
+// (8.1 us at 2^19 and 8.4 at 2^20 for the two kernels); 2^20 bfloat16 6.8. The
+// compensated sum's longer chains lose from 2^20 on (8.2 against 7.7 us; 2^19: 7.3
+// and 7.7), so it stops at 2^19. The call that takes over is kept off the common
+// path: in one loop with it, 2^19 binary32 took 6.4 to 7.0 us and 2^20 bfloat16 7.3
+// to 7.8. The slot is looked at after the elements are requested (before: 6.6 and 6.9).
 constexpr int PRES_BLOCK = 256;
 constexpr int PRES_LOG2 = 12;
 constexpr int PRES_MAX_SEGMENTS = 64;
 constexpr int64_t PRES_SHORT_MAX = (int64_t)PRES_MAX_SEGMENTS << PRES_LOG2;
+// Polls (about 1 us each) before a block takes another segment: longer than
+// blocks of one launch start apart on a free device, short beside a foreign
+// kernel that keeps some of them out.
+constexpr uint32_t PRES_PATIENCE = 1u << 10;
+
+// Wavefront 0, lane l: wait for the sum of segment l. Returns the mask of the
+// segments without one after `patience` polls; 0: *total is the sum of all,
+// in every lane, in an order that depends only on nseg.
+template <int ACC>
+__device__ __forceinline__ uint64_t gather_segments(const unsigned long long* words, uint32_t ep, int nseg,
+                                                    uint32_t patience, Acc<ACC>* total) {
+  const int lane = threadIdx.x & 63;
+  float f[2] = {0.0f, 0.0f};
+  bool have = lane >= nseg;
+  for (uint32_t spin = 0;; ++spin) {
+    if (!have) {
+      have = true;
+#pragma unroll
+      for (int w = 0; w < Tagged<ACC>::WORDS; ++w) {
+        const unsigned long long v =
+            __hip_atomic_load(words + 2 * lane + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        f[w] = f32_bits((uint32_t)v);
+        have = have && (uint32_t)(v >> 32) == ep;
+      }
+    }
+    const uint64_t missing = __ballot(!have);
+    if (missing && spin < patience) {
+      __builtin_amdgcn_s_sleep(1);
+      continue;
+    }
+    if (missing) return missing;
+    Acc<ACC> v;
+    if (lane < nseg) v = Tagged<ACC>::join(f);
+    else v.zero();
+    *total = wave_reduce<ACC>(v);
+    return 0;
+  }
+}
+
+// One thread: publish a segment's sum in place of the words seen before; true
+// if the segment is now this block's. (Each word on its own: two blocks that
+// both find a word unpublished have summed the same elements.)
+template <int ACC>
+__device__ __forceinline__ bool claim_tagged(unsigned long long* words, unsigned long long (&seen)[2], uint32_t ep,
+                                             const Acc<ACC>& v) {
+  float f[2];
+  Tagged<ACC>::split(v, f);
+  bool won[2] = {false, false};
+#pragma unroll
+  for (int w = 0; w < Tagged<ACC>::WORDS; ++w)
+    if ((uint32_t)(seen[w] >> 32) != ep)
+      won[w] = __hip_atomic_compare_exchange_strong(words + w, &seen[w], ((unsigned long long)ep << 32) | bits_f32(f[w]),
+                                                    __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return won[0];
+}
+
+// What the blocks of one call meet over.
+template <int ACC>
+struct PlainExchange {
+  PlainResidentWs w;
+  uint32_t ep;  // the call's tag: never 0, the value of a slot that was never written
+  int nseg;
+  Acc<ACC>* slots;
+  RowRes* s_bcast;
+  uint64_t* s_mine;  // the segments that are this block's
+  int* s_next;       // the one to take next, -1: every sum is known
+
+  // The slot's words, before the segment's sum is known; thread 0.
+  __device__ __forceinline__ void look(int seg, unsigned long long (&seen)[2]) const {
+    seen[0] = seen[1] = 0;
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int k = 0; k < Tagged<ACC>::WORDS; ++k)
+        seen[k] = __hip_atomic_load(w.slots + 2 * seg + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+
+  // Publish the segment's sum, then wait for the others: the result in *s_bcast
+  // and this block's arrival, or the segment to take next. Every thread.
+  __device__ __forceinline__ int meet(int seg, unsigned long long (&seen)[2], const Acc<ACC>& tot, uint64_t& mine,
+                                      uint32_t patience) const {
+    if (threadIdx.x < 64) {
+      bool won = false;
+      if (threadIdx.x == 0) won = claim_tagged<ACC>(w.slots + 2 * seg, seen, ep, tot);
+      Acc<ACC> total;
+      uint64_t missing = gather_segments<ACC>(w.slots, ep, nseg, patience, &total);
+      if (won) mine |= 1ull << seg;
+      if (threadIdx.x == 0) {
+        *s_mine = mine;
+        *s_next = -1;
+        if (missing) {
+          // blocks that wait for the same segments take different ones first
+          for (int skip = blockIdx.x % __popcll(missing); skip > 0; --skip) missing &= missing - 1;
+          *s_next = __ffsll((unsigned long long)missing) - 1;
+        } else {
+          *s_bcast = RowMap<ACC>::of(total).result();
+          if (__hip_atomic_fetch_add(w.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == w.blocks - 1) {
+            __hip_atomic_store(w.arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(w.call, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+      }
+    }
+    lds_barrier();
+    return __builtin_amdgcn_readfirstlane(*s_next);
+  }
+};
 
 template <int DTI, int DTO, int ACC, int BLOCK, int LOG2>
 __global__ void __launch_bounds__(BLOCK) plain_resident_kernel(RowDesc d, PlainResidentWs w) {
   __shared__ Acc<ACC> slots[MAX_WAVES];
   __shared__ RowRes s_bcast;
-  // the tag is never 0, the value of a slot that was never written; the last
-  // block to arrive moves the call number on once every block has read it
+  __shared__ uint64_t s_mine;
+  __shared__ int s_next;
   const unsigned long long call = __hip_atomic_load(w.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const ResExchange x{w.slots, nullptr, w.arrivals, (uint32_t)(call % 0xFFFFFFFFull) + 1u, w.error, w.stall, w.call};
-  resident_unit<DTI, DTO, ACC, BLOCK, LOG2, 1, true>(d, blockIdx.x, x, slots, &s_bcast, nullptr);
+  const PlainExchange<ACC> x{w,     (uint32_t)(call % 0xFFFFFFFFull) + 1u, (int)((d.n + (1 << LOG2) - 1) >> LOG2),
+                             slots, &s_bcast, &s_mine, &s_next};
+  const int seg = blockIdx.x;
+  unsigned long long seen[2];
+  Held<DTI, DTO, ACC, BLOCK, LOG2> h;
+  h.load(d, seg);
+  x.look(seg, seen);
+  const Acc<ACC> tot = h.sum(slots);
+  uint64_t mine = 0;
+  int next = -1;
+  if (x.nseg > 1) {
+    next = x.meet(seg, seen, tot, mine, PRES_PATIENCE);
+  } else {  // nothing to exchange
+    if (threadIdx.x == 0) {
+      s_bcast = RowMap<ACC>::of(tot).result();
+      s_mine = 1;
+    }
+    lds_barrier();
+  }
+  if (__builtin_expect(next < 0, 1)) {
+    if (uniform64((int64_t)s_mine) != 0) h.divide(RowMap<ACC>::of(s_bcast));
+  } else {
+    while (next >= 0) {
+      const int take = next;
+      lds_barrier();  // slots, s_mine and s_next are reused
+      x.look(take, seen);
+      h.load(d, take);
+      next = x.meet(take, seen, h.sum(slots), mine, 1);  // having waited once, one after the other
+    }
+    for (uint64_t own = (uint64_t)uniform64((int64_t)s_mine); own; own &= own - 1) {
+      h.load(d, __ffsll((unsigned long long)own) - 1);
+      h.divide(RowMap<ACC>::of(s_bcast));
+    }
+  }
   if (threadIdx.x == 0 && blockIdx.x == 0) w.sum_out[0] = s_bcast.a;  // the invariant, for nrm_get_last_sum
 }
 
 template <int ACC, int BLOCK, int LOG2>
-hipError_t plain_resident_acc(const RowDesc& d, const PlainResidentWs& w, hipStream_t s) {
-  const unsigned grid = (unsigned)((d.n + (int64_t(1) << LOG2) - 1) >> LOG2);
+hipError_t plain_resident_acc(const RowDesc& d, PlainResidentWs w, hipStream_t s) {
+  const unsigned segments = (unsigned)((d.n + (int64_t(1) << LOG2) - 1) >> LOG2);
+  if (w.blocks == 0 || w.blocks > segments) w.blocks = segments;
 #define NRM_PR(I, O) \
-  hipLaunchKernelGGL((plain_resident_kernel<I, O, ACC, BLOCK, LOG2>), dim3(grid), dim3(BLOCK), 0, s, d, w)
+  hipLaunchKernelGGL((plain_resident_kernel<I, O, ACC, BLOCK, LOG2>), dim3(w.blocks), dim3(BLOCK), 0, s, d, w)
   switch (d.in_dt * 3 + d.out_dt) {
     case NRM_F32 * 3 + NRM_F32: NRM_PR(NRM_F32, NRM_F32); break;
     case NRM_F32 * 3 + NRM_BF16: NRM_PR(NRM_F32, NRM_BF16); break;

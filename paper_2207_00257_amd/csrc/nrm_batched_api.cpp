@@ -681,7 +681,6 @@ int nrm_get_device_error(nrm_ctx* c, void* stream) {
       if (e == hipSuccess)
         e = hipMemset(c->batch.args.tile_arrivals, 0, sizeof(unsigned) * (size_t)c->batch.cap_items);
     }
-    if (e == hipSuccess) e = hipMemset(c->res.arrivals, 0, sizeof(unsigned));
     if (e != hipSuccess) return hip_fail(e, "clearing the arrival counts");
   }
   std::string why;

@@ -552,8 +552,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
       continue;
     }
     const uint32_t tag = dq_tag(c.seq);
-    const ResExchange x{q->tagged[c.slot], q->total[c.slot], &q->arrivals[c.slot], tag, &q->error, &q->stall,
-                        nullptr};
+    const ResExchange x{q->tagged[c.slot], q->total[c.slot], &q->arrivals[c.slot], tag, &q->error, &q->stall};
     if (c.d.n <= DQ_RESIDENT_MAX) {
       dispatch_resident<ACC>(c.d, (int)c.part, x, slots, &s_bcast, nullptr);
       dq_finish(a, c, (unsigned)c.units);

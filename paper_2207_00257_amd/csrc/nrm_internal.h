@@ -113,15 +113,16 @@ hipError_t launch_small(const void* in, int in_dt, void* out, int out_dt, int64_
 // The plain path's single-launch form for mid-size n (nrm_batched.hip): one
 // block per segment of the input held in registers across an exchange of the
 // segment sums; n <= plain_resident_capacity(acc). Workspace, zero-initialized:
-// the segments' tagged partials (16 bytes each), the arrival count, the call
-// number, the stall marker and error word, and the sum for nrm_get_last_sum.
+// the segments' tagged sums (16 bytes each), the count of blocks that have
+// arrived, the call number, and the sum for nrm_get_last_sum. `blocks` bounds
+// the launch's blocks (0: one per segment); fewer take the remaining segments
+// over, as they do when not all of them can run.
 struct PlainResidentWs {
   unsigned long long* slots;  // 2 x 64 words
   unsigned* arrivals;         // 0 between calls
   unsigned long long* call;
-  unsigned long long* stall;
-  int* error;
   float* sum_out;
+  unsigned blocks;
 };
 int64_t plain_resident_capacity(int acc);
 hipError_t launch_plain_resident(const void* in, int in_dt, void* out, int out_dt, int64_t n, int acc,

@@ -225,7 +225,6 @@ struct ResExchange {
   uint32_t ep;                // this call's number
   int* error;                 // device error word (NRM_DEVERR_STALL)
   unsigned long long* stall;  // the number of the last call in which a wait gave up
-  unsigned long long* call;   // DIRECT: the call counter the last arrival moves on
 };
 
 template <int ACC>
@@ -324,87 +323,106 @@ __device__ __forceinline__ Acc<ACC> gather_row(const ResExchange& x, int nseg) {
   return wave_reduce<ACC>(v[0]);
 }
 
+// A segment of 2^LOG2 elements of a row in a BLOCK-thread block's registers:
+// read, summed over the block, and divided from the registers.
+template <int DTI, int DTO, int ACC, int BLOCK, int LOG2>
+struct Held {
+  static constexpr int VEC = Elem<DTI>::VEC;
+  static constexpr int KB = (1 << LOG2) / (BLOCK * VEC);
+  static_assert(KB >= 1 && KB * BLOCK * VEC == (1 << LOG2), "a segment is whole vectors per thread");
+  // chains per thread: 8 binary32, 4 of the two-float kinds (registers)
+  static constexpr int NA_MAX = ACC == NRM_ACC_F32 ? 8 : 4;
+  static constexpr int NA = KB * VEC < NA_MAX ? KB * VEC : NA_MAX;
+  static constexpr int S = 1 << LOG2;
+
+  int t, ti;  // this thread, and the tail element it may hold
+  char* out_seg;
+  Geom g;
+  bool has_head, has_tail;
+  u4 r[KB];
+  float xh, xt;
+
+  __device__ __forceinline__ void load(const RowDesc& d, int seg) {
+    t = thread_index();
+    const int64_t b = (int64_t)seg << LOG2;
+    const int n = d.n - b < S ? (int)(d.n - b) : S;
+    const char* in_seg = d.in + b * Elem<DTI>::SIZE;
+    out_seg = d.out + b * Elem<DTO>::SIZE;
+    g = geometry<DTI>(in_seg, n);
+    const u4* body = reinterpret_cast<const u4*>(in_seg + g.head * Elem<DTI>::SIZE);
+    has_head = t < g.head;
+    ti = g.tail_begin + t;
+    has_tail = ti < n;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      const int v = t + k * BLOCK;
+      if (v < g.nvec) r[k] = load_vec<true>(body + v);
+    }
+    xh = has_head ? load_one<DTI>(in_seg, t) : 0.0f;
+    xt = has_tail ? load_one<DTI>(in_seg, ti) : 0.0f;
+  }
+
+  // The segment's sum; valid in thread 0.
+  __device__ __forceinline__ Acc<ACC> sum(Acc<ACC>* slots) const {
+    Acc<ACC> acc[NA];
+#pragma unroll
+    for (int k = 0; k < NA; ++k) acc[k].zero();
+    if constexpr (ACC == ACC_SOFTMAX) {
+      softmax_add_held<DTI, NA, KB>(acc, r, t, BLOCK, g.nvec);
+    } else {
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        if (t + k * BLOCK < g.nvec) {
+          float xv[VEC];
+          widen<DTI>(r[k], xv);
+#pragma unroll
+          for (int c = 0; c < VEC; ++c) acc[(k * VEC + c) % NA].add(xv[c]);
+        }
+      }
+    }
+    if (has_head) acc[0].add(xh);
+    if (has_tail) acc[0].add(xt);
+    merge_chains<ACC, NA>(acc);
+    return block_reduce<ACC>(acc[0], slots);
+  }
+
+  __device__ __forceinline__ void divide(const RowMap<ACC>& f) const {
+    const bool vec_ok = out_vector_ok<DTI, DTO>(out_seg, g.head);
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      const int v = t + k * BLOCK;
+      if (v < g.nvec) {
+        float xv[VEC], q[VEC];
+        widen<DTI>(r[k], xv);
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) q[c] = f(xv[c]);
+        store_quotients<DTI, DTO>(out_seg, g.head, v, vec_ok, q);
+      }
+    }
+    if (has_head) store_one<DTO>(out_seg, t, f(xh));
+    if (has_tail) store_one<DTO>(out_seg, ti, f(xt));
+  }
+};
+
 // One resident segment of 2^LOG2 elements held by a BLOCK-thread block:
 // read into registers, block sum, exchange with the row's other segments,
 // divide from the registers, write. The row's result (RowMap) is left in
 // *s_bcast; lse, when given, receives the softmax row's log-sum-exp (from
-// segment 0).
-//
-// DIRECT: every block of the row reads all partials itself (one round trip:
-// the lowest latency for a single row of few segments) instead of waiting for
-// the last arrival's total (fewer polls: the better throughput for a batch);
-// the arrival count then only finds the last block, which moves the call
-// number on. ALONE: the row is this one segment (no exchange is compiled in).
-template <int DTI, int DTO, int ACC, int BLOCK, int LOG2, int PER_LANE, bool DIRECT = false, bool ALONE = false>
+// segment 0). ALONE: the row is this one segment (no exchange is compiled in).
+template <int DTI, int DTO, int ACC, int BLOCK, int LOG2, int PER_LANE, bool ALONE = false>
 __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const ResExchange& x, Acc<ACC>* slots,
                                               RowRes* s_bcast, float* lse_row) {
-  constexpr int VEC = Elem<DTI>::VEC;
-  constexpr int KB = (1 << LOG2) / (BLOCK * VEC);
-  static_assert(KB >= 1 && KB * BLOCK * VEC == (1 << LOG2), "a segment is whole vectors per thread");
-  // chains per thread: 8 binary32, 4 of the two-float kinds (registers)
-  constexpr int NA_MAX = ACC == NRM_ACC_F32 ? 8 : 4;
-  constexpr int NA = KB * VEC < NA_MAX ? KB * VEC : NA_MAX;
-  const int t = thread_index();
-  constexpr int S = 1 << LOG2;
-  const int64_t b = (int64_t)seg << LOG2;
-  const int n = d.n - b < S ? (int)(d.n - b) : S;
-  const int nseg = (int)((d.n + S - 1) >> LOG2);
-  const char* in_seg = d.in + b * Elem<DTI>::SIZE;
-  char* out_seg = d.out + b * Elem<DTO>::SIZE;
-  const Geom g = geometry<DTI>(in_seg, n);
-  const u4* body = reinterpret_cast<const u4*>(in_seg + g.head * Elem<DTI>::SIZE);
-  const bool has_head = t < g.head;
-  const int ti = g.tail_begin + t;
-  const bool has_tail = ti < n;
-  u4 r[KB];
-#pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    const int v = t + k * BLOCK;
-    if (v < g.nvec) r[k] = load_vec<true>(body + v);
-  }
-  const float xh = has_head ? load_one<DTI>(in_seg, t) : 0.0f;
-  const float xt = has_tail ? load_one<DTI>(in_seg, ti) : 0.0f;
-  Acc<ACC> acc[NA];
-#pragma unroll
-  for (int k = 0; k < NA; ++k) acc[k].zero();
-  if constexpr (ACC == ACC_SOFTMAX) {
-    softmax_add_held<DTI, NA, KB>(acc, r, t, BLOCK, g.nvec);
-  } else {
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      if (t + k * BLOCK < g.nvec) {
-        float xv[VEC];
-        widen<DTI>(r[k], xv);
-#pragma unroll
-        for (int c = 0; c < VEC; ++c) acc[(k * VEC + c) % NA].add(xv[c]);
-      }
-    }
-  }
-  if (has_head) acc[0].add(xh);
-  if (has_tail) acc[0].add(xt);
-  merge_chains<ACC, NA>(acc);
-  const Acc<ACC> tot = block_reduce<ACC>(acc[0], slots);
+  Held<DTI, DTO, ACC, BLOCK, LOG2> h;
+  h.load(d, seg);
+  const int t = h.t;
+  const int nseg = (int)((d.n + h.S - 1) >> LOG2);
+  const Acc<ACC> tot = h.sum(slots);
   if (ALONE || nseg == 1) {
     if (t == 0) {
       const RowMap<ACC> f0 = RowMap<ACC>::of(tot);
       *s_bcast = f0.result();
       if constexpr (ACC == ACC_SOFTMAX) {
         if (lse_row) *lse_row = f0.lse();
-      }
-    }
-  } else if (DIRECT && t < 64) {
-    if (t == 0) publish_tagged<ACC>(x.slots + 2 * seg, x.ep, tot);
-    const Acc<ACC> total = gather_row<ACC, PER_LANE>(x, nseg);
-    if (t == 0) {
-      const RowMap<ACC> f0 = RowMap<ACC>::of(total);
-      *s_bcast = f0.result();
-      if constexpr (ACC == ACC_SOFTMAX) {
-        if (lse_row && seg == 0) *lse_row = f0.lse();
-      }
-      // after this block's reads of the tags: the last one moves the call on
-      if (__hip_atomic_fetch_add(x.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nseg - 1) {
-        __hip_atomic_store(x.arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(x.call, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   } else if (t < 64) {
@@ -433,30 +451,16 @@ __device__ __forceinline__ void resident_unit(const RowDesc& d, int seg, const R
     }
   }
   lds_barrier();
-  const RowMap<ACC> f = RowMap<ACC>::of(*s_bcast);
-  const bool vec_ok = out_vector_ok<DTI, DTO>(out_seg, g.head);
-#pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    const int v = t + k * BLOCK;
-    if (v < g.nvec) {
-      float xv[VEC], q[VEC];
-      widen<DTI>(r[k], xv);
-#pragma unroll
-      for (int c = 0; c < VEC; ++c) q[c] = f(xv[c]);
-      store_quotients<DTI, DTO>(out_seg, g.head, v, vec_ok, q);
-    }
-  }
-  if (has_head) store_one<DTO>(out_seg, t, f(xh));
-  if (has_tail) store_one<DTO>(out_seg, ti, f(xt));
+  h.divide(RowMap<ACC>::of(*s_bcast));
 }
 
 template <int ACC, bool ALONE = false>
 __device__ __forceinline__ void dispatch_resident(const RowDesc& d, int seg, const ResExchange& x, Acc<ACC>* slots,
                                                   RowRes* s_bcast, float* lse_row) {
   if constexpr (ACC == ACC_SOFTMAX) {
-    resident_unit<NRM_F32, NRM_F32, ACC, RES_BLOCK, RES_LOG2, 1, false, ALONE>(d, seg, x, slots, s_bcast, lse_row);
+    resident_unit<NRM_F32, NRM_F32, ACC, RES_BLOCK, RES_LOG2, 1, ALONE>(d, seg, x, slots, s_bcast, lse_row);
   } else {
-#define NRM_RU(I, O) return resident_unit<I, O, ACC, RES_BLOCK, RES_LOG2, 1, false, ALONE>(d, seg, x, slots, s_bcast, lse_row)
+#define NRM_RU(I, O) return resident_unit<I, O, ACC, RES_BLOCK, RES_LOG2, 1, ALONE>(d, seg, x, slots, s_bcast, lse_row)
     switch (d.in_dt * 3 + d.out_dt) {
       case NRM_F32 * 3 + NRM_F32: NRM_RU(NRM_F32, NRM_F32);
       case NRM_F32 * 3 + NRM_BF16: NRM_RU(NRM_F32, NRM_BF16);
