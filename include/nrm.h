@@ -130,7 +130,8 @@ typedef struct {
  * dtypes and start alignment modulo 128 bytes, never on the other rows.
  * block, unroll, map_unroll, grid, short_regs, map_block and map_grid shape the
  * three launches that take the longer rows when resident_segments is 0; with
- * resident rows those rows are units of one persistent kernel. */
+ * resident rows those rows are units of one persistent kernel, or in a large batch
+ * mostly of them three launches, of which the map_ parameters shape the divide. */
 typedef struct {
   int32_t block;       /* threads per block: 64..1024, multiple of 64 */
   int32_t unroll;      /* tile sums: 16-byte vectors per thread per iteration: 1, 2, 4, 8 */
@@ -140,8 +141,8 @@ typedef struct {
   int32_t short_regs;  /* 16-byte vectors per thread held in registers by a single-pass row:
                           1, 2, 4 or 8; rows with n <= block * short_regs * 4 take one pass
                           (one read, one write) */
-  int32_t graph;       /* 1 (default): batches of at least 2^27 elements (capacity, in the CSR forms)
-                          replay a hipGraph of the launch sequence, captured on a stream of the
+  int32_t graph;       /* 1 (default): batches of at least 2^27 elements (capacity, in the CSR forms),
+                          unless mostly of long rows, replay a hipGraph of the launch sequence, captured on a stream of the
                           library's own on first use (smaller ones are launched kernel by kernel, which
                           costs the host less than a replay); 0: every batch is launched kernel by kernel */
   int32_t map_block;   /* threads per block of the divide phase: 64..1024, multiple of 64 */

@@ -111,6 +111,7 @@ struct BatchArgs {
   // cut into segments of 2^RES_LOG2 elements, one entry each, each held in one
   // block's registers from its read to its write
   int res_on;
+  int apart;  // long rows in launches of their own, not in the resident rows' kernel
   // by a row's first entry: its entries' partials (two tagged words each),
   // its total (two tagged words), and the count of its published partials (0
   // between calls)

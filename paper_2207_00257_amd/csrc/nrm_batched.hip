@@ -17,6 +17,9 @@
 //                        of the rows of up to 2^20 elements (held on chip
 //                        between their read and their write), then the tiles
 //                        of the long rows again for the divide.
+// In a large batch mostly of long rows, that kernel takes the segments only and
+//   batch_tile_sums_kernel, batch_tile_totals_kernel, batch_phase2_kernel
+// take the long rows, each with as many blocks as stream best.
 // With resident_segments = 0 the lists are instead walked by three launches:
 //   batch_phase1_kernel  single-pass rows and tile sums;
 //   batch_rowsum_kernel  one block per long row merges the row's tile sums in
@@ -455,6 +458,25 @@ __device__ __forceinline__ Acc<ACC> gather_tiles(const ResExchange& x, int64_t c
   return v;
 }
 
+// The sum of one tile of a long row; valid in thread 0. The last keep_tiles
+// tiles of a batch are read with a temporal hint (keep): the divide finds them
+// in the last-level cache.
+template <int ACC>
+__device__ __forceinline__ Acc<ACC> tile_sum(const BatchArgs& a, const Item& it, bool keep, Acc<ACC>* slots) {
+  const RowDesc& d = it.d;
+  const int64_t b = (int64_t)it.tile << a.tile_log2;
+  const int64_t e = b + a.tile < d.n ? b + a.tile : d.n;
+  Acc<ACC> p;
+  p.zero();
+  for (int64_t c = b; c < e; c += TILE_PART) {
+    const int64_t ce = c + TILE_PART < e ? c + TILE_PART : e;
+    p.merge(keep ? dispatch_tile_reduce<ACC, TILE_U, false, TILE_NA>(d, c, ce, slots)
+                 : dispatch_tile_reduce<ACC, TILE_U, true, TILE_NA>(d, c, ce, slots));
+    if (ce < e) lds_barrier();  // slots are reused
+  }
+  return p;
+}
+
 // The entries that one block of batch_rows_kernel appended: where in the list,
 // and which in row order.
 struct ListRange {
@@ -506,6 +528,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
   // (entries past the capacity were not written; in row order they are passed
   // over one by one)
   if (n_long > a.cap_items) n_long = a.cap_items;
+  if (a.apart) n_long = 0;
   if (n_short > a.cap_items && ordered == 0) n_short = a.cap_items;
   if (blockIdx.x == 0 && threadIdx.x == 0) end_call(a, call);
   const int64_t units = n_long + n_short;
@@ -549,19 +572,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
       const RowDesc& d = it.d;
       if (u < n_long) {
         const int64_t first = u - it.tile;
-        const int64_t b = (int64_t)it.tile << a.tile_log2;
-        const int64_t e = b + a.tile < d.n ? b + a.tile : d.n;
-        // the last keep_tiles tiles are read with a temporal hint: the
-        // divide finds them in the last-level cache
-        const bool keep = u >= n_long - a.keep_tiles;
-        Acc<ACC> p;
-        p.zero();
-        for (int64_t c = b; c < e; c += TILE_PART) {
-          const int64_t ce = c + TILE_PART < e ? c + TILE_PART : e;
-          p.merge(keep ? dispatch_tile_reduce<ACC, TILE_U, false, TILE_NA>(d, c, ce, slots)
-                       : dispatch_tile_reduce<ACC, TILE_U, true, TILE_NA>(d, c, ce, slots));
-          if (ce < e) lds_barrier();  // slots are reused
-        }
+        const Acc<ACC> p = tile_sum<ACC>(a, it, u >= n_long - a.keep_tiles, slots);
         const ResExchange x{a.tile_tagged + 2 * first, a.tile_total + 2 * first, a.tile_arrivals + first, ep, a.error, stall};
         const int64_t count = (d.n + a.tile - 1) >> a.tile_log2;
         if (threadIdx.x == 0) {
@@ -610,6 +621,58 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
     if (threadIdx.x == 0) s_bcast = RowMap<ACC>::of(wait_tagged<ACC>(x, x.total)).result();
     lds_barrier();
     dispatch_tile_map<ACC, TILE_MAP_U>(d, b, e, RowMap<ACC>::of(s_bcast));
+  }
+}
+
+// ---- the long rows in launches of their own --------------------------------------------------
+// A large batch mostly of long rows (args.apart): the same tile sums, published
+// in the same tagged words and merged in the same order, so that a row's bits do
+// not depend on it, then the divide by batch_phase2_kernel.
+//
+// HBM bounds it, three transfers. The persistent kernel takes the tiles from a
+// counter, which serves one per 14 to 17 ns, holds 80 registers for the segments,
+// and waits for each unit's row total: 16 rows of 20,000,000 binary32 676 us there,
+// 611 us here (5.8 TB/s over 3.84 GB less what the cache keeps), bfloat16 424 and
+// 318 us. Small batches lose here to the launches' starts, and those with wider
+// outputs than inputs to phase 2's two stores per vector: see the host's rule.
+
+template <int ACC>
+__global__ void __launch_bounds__(RES_BLOCK) batch_tile_sums_kernel(BatchArgs a) {
+  __shared__ Acc<ACC> slots[MAX_WAVES];
+  const int64_t call = a.cnt[CNT_CALL_RUN];
+  const int64_t listed = list_counters(a, call)[LIST_TILES * CNT_LINE];
+  const int64_t n_long = listed < a.cap_items ? listed : a.cap_items;
+  for (int64_t pos = blockIdx.x; pos < n_long; pos += gridDim.x) {
+    const Item it = uniform_item(a.tiles[pos]);
+    if (it.row < 0) continue;
+    const Acc<ACC> p = tile_sum<ACC>(a, it, pos >= n_long - a.keep_tiles, slots);
+    if (threadIdx.x == 0) publish_tagged<ACC>(a.tile_tagged + 2 * pos, call_tag(call), p);
+    lds_barrier();  // slots are reused
+  }
+}
+
+// One block per long row at a time.
+template <int ACC>
+__global__ void __launch_bounds__(RES_BLOCK) batch_tile_totals_kernel(BatchArgs a) {
+  __shared__ Acc<ACC> slots[MAX_WAVES];
+  __shared__ Acc<ACC> rounds[TILE_ROUNDS];
+  const int64_t call = a.cnt[CNT_CALL_RUN];
+  const int64_t n_rows = list_counters(a, call)[LIST_LONG_ROWS * CNT_LINE];
+  float* lse = lse_out(a);
+  for (int64_t k = blockIdx.x; k < n_rows; k += gridDim.x) {
+    const int64_t first = a.lrow_first[k];
+    const Item it = uniform_item(a.tiles[first]);
+    const ResExchange x{a.tile_tagged + 2 * first, nullptr, nullptr, call_tag(call), a.error,
+                        reinterpret_cast<unsigned long long*>(a.cnt + CNT_STALL)};
+    const Acc<ACC> total = gather_tiles<ACC>(x, (it.d.n + a.tile - 1) >> a.tile_log2, slots, rounds);
+    if (threadIdx.x == 0) {
+      const RowMap<ACC> f = RowMap<ACC>::of(total);
+      a.results[first] = f.result();
+      if constexpr (ACC == ACC_SOFTMAX) {
+        if (lse) lse[it.row] = f.lse();
+      }
+    }
+    lds_barrier();  // rounds are reused
   }
 }
 
@@ -710,6 +773,10 @@ hipError_t phase1_u(const BatchPlan& p, const BatchArgs& a, hipStream_t s) {
 }
 
 constexpr int64_t ROWSUM_GRID = 1024;
+// the long rows' own launches: 16 blocks per CU, a tile at a time (four per CU:
+// compensated sums of 200 rows of 2^18 to 2^22 binary32 625 us, with 16 602); a
+// block per row
+constexpr unsigned SUMS_GRID = 4096, TOTALS_GRID = 256;
 
 template <int ACC>
 hipError_t rowsum_acc(const BatchPlan& p, const BatchArgs& a, hipStream_t s) {
@@ -1057,7 +1124,7 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
       if (lane == 0) {
         if (!fits) {
           atomicOr(a.error, NRM_DEVERR_CAPACITY);
-        } else if (is_long && !a.res_on) {
+        } else if (is_long && (!a.res_on || a.apart)) {
           unsigned long long* lists = reinterpret_cast<unsigned long long*>(list_counters(a, call));
           a.lrow_first[__hip_atomic_fetch_add(lists + LIST_LONG_ROWS * CNT_LINE, 1ull, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT)] = first;
@@ -1083,7 +1150,11 @@ hipError_t launch_lists(const BatchPlan& p, const BatchArgs& a, hipStream_t s) {
   if (e != hipSuccess || !p.lists) return e;
   if (a.res_on) {
     hipLaunchKernelGGL((batch_resident_kernel<ACC>), dim3((unsigned)p.res_grid), dim3(RES_BLOCK), 0, s, a);
-    return hipGetLastError();
+    e = hipGetLastError();
+    if (e != hipSuccess || !a.apart) return e;
+    hipLaunchKernelGGL((batch_tile_sums_kernel<ACC>), dim3(SUMS_GRID), dim3(RES_BLOCK), 0, s, a);
+    hipLaunchKernelGGL((batch_tile_totals_kernel<ACC>), dim3(TOTALS_GRID), dim3(RES_BLOCK), 0, s, a);
+    return phase2_acc<ACC>(p, a, s);
   }
   e = phase1_u<ACC>(p, a, s);
   if (e != hipSuccess) return e;

@@ -36,6 +36,19 @@ int64_t align_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 // that on the device (2^24 binary32 elements read and written: about 21 us).
 constexpr int64_t kGraphElems = int64_t(1) << 27;
 
+// Batches of at least this many elements, most of them in long rows, run the
+// long rows in launches of their own (the results are the same). us per call on
+// MI355X, in the persistent kernel and apart:
+//                         rows of 2,000,000, 32       64         128
+//   binary32                        128 and 127  258 and 246  545 and 492
+//   bfloat16                         92 and  73  189 and 135
+//   bfloat16 to binary32             99 and 133  218 and 217
+// and 16 rows of 20,000,000 676 and 611, 424 and 318, 569 and 551. (At most 8 rows
+// are also a little faster apart, 29 and 26 us for 4 of them, for three launches
+// more on the host.)
+constexpr int64_t kApartElems = int64_t(1) << 26;
+constexpr int64_t kApartElemsWide = int64_t(1) << 27;  // with outputs wider than inputs among them
+
 nrm_batch_params default_batch_params() {
   nrm_batch_params p;
   std::memset(&p, 0, sizeof(p));
@@ -246,6 +259,7 @@ BatchArgs args_of(const nrm_ctx* c) {
   a.keep_tiles = ((int64_t)p.keep_mib << 20) / (a.tile * 4);
   a.wave_max = p.wave_max;
   a.res_on = p.resident_segments > 0;
+  a.apart = 0;
   return a;
 }
 
@@ -372,10 +386,10 @@ int keep_table(BatchWorkspace& w, const nrm_row* table, int64_t nrows, const Row
 }
 
 // Run the launch sequence on `s` for a batch of at most `elems` elements whose
-// longest row has at most `longest`. A row table is staged in the next ring
-// buffer first.
+// longest row has at most `longest`; `wide`: some rows' outputs are wider than
+// their inputs. A row table is staged in the next ring buffer first.
 int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nrows, int64_t elems, int64_t longest,
-              int acc, hipStream_t s) {
+              bool wide, int acc, hipStream_t s) {
   BatchWorkspace& w = c->batch;
   hipError_t e;
   if (w.dirty) {
@@ -386,7 +400,8 @@ int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nr
   a.header = h;
   cut_rows(c->bparams, nrows, elems, &a.header);
   BatchPlan p = plan_of(c, a.header, nrows, elems, longest, acc);
-  bool replay = c->bparams.graph && elems >= kGraphElems;
+  a.apart = a.res_on && elems >= (wide ? kApartElemsWide : kApartElems) && elems / nrows > a.short_max;
+  bool replay = c->bparams.graph && elems >= kGraphElems && !a.apart;
   bool ring = replay || table;
   if (ring) {
     hipStreamCaptureStatus state = hipStreamCaptureStatusNone;
@@ -591,7 +606,8 @@ int run_csr(nrm_ctx* c, void* out, int out_dtype, const void* in, int in_dtype, 
   h.csr_out = static_cast<char*>(out);
   h.capacity = capacity;
   h.lse = lse;
-  return run_batch(c, h, nullptr, rows, capacity, capacity, acc, s);
+  const bool wide = nrm::dtype_size(out_dtype) > nrm::dtype_size(in_dtype);
+  return run_batch(c, h, nullptr, rows, capacity, capacity, wide, acc, s);
 }
 }  // namespace
 
@@ -618,6 +634,7 @@ int nrm_normalize_rows(nrm_ctx* c, const nrm_row* rows, int64_t nrows, int accum
   if (nrows > INT32_MAX) return fail(NRM_EINVAL, "more than 2^31 - 1 rows");
   if (!rows) return fail(NRM_EINVAL, "rows is NULL");
   int64_t total = 0, longest = 0;
+  bool wide = false;
   for (int64_t r = 0; r < nrows; ++r) {
     const nrm_row& d = rows[r];
     if (d.n < 0) return fail(NRM_EINVAL, "row with n < 0");
@@ -633,6 +650,7 @@ int nrm_normalize_rows(nrm_ctx* c, const nrm_row* rows, int64_t nrows, int accum
       return fail(NRM_EOVERLAP, "a row's in and out overlap without being the same array");
     total += d.n;
     longest = std::max(longest, d.n);
+    wide = wide || so > si;
   }
   if (!c) {
     int st = nrm::default_ctx(&c);
@@ -648,7 +666,7 @@ int nrm_normalize_rows(nrm_ctx* c, const nrm_row* rows, int64_t nrows, int accum
   std::memset(&h, 0, sizeof(h));
   h.nrows = nrows;
   h.mode = nrm::BATCH_TABLE;
-  return run_batch(c, h, rows, nrows, total, longest, accum, static_cast<hipStream_t>(stream));
+  return run_batch(c, h, rows, nrows, total, longest, wide, accum, static_cast<hipStream_t>(stream));
 }
 
 int nrm_get_device_error(nrm_ctx* c, void* stream) {

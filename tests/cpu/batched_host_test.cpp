@@ -156,14 +156,14 @@ static void test_captured_tables() {
       CHECK(captured[k][r].in == reinterpret_cast<const char*>(in.data() + 100 * k + r * (10 + k)));
     }
   const int launches = g_launches;
-  const int64_t offsets[2] = {0, 10};
-  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets, 1, kGraphElems, NRM_ACC_F32,
+  const std::vector<int64_t> offsets(201, 0);
+  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 200, kGraphElems, NRM_ACC_F32,
                                  nullptr) != NRM_OK);  // a replay: no graph can be made here
   g_capturing = true;
-  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets, 1, kGraphElems, NRM_ACC_F32,
+  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 200, kGraphElems, NRM_ACC_F32,
                                  nullptr) == NRM_OK);
   g_capturing = false;
-  CHECK(g_launches == launches + 1 && g_args.header.offsets == offsets);
+  CHECK(g_launches == launches + 1 && g_args.header.offsets == offsets.data());
 }
 
 // A call whose later launches fail leaves its list entries behind: the next
