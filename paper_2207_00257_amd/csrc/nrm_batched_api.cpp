@@ -336,15 +336,18 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 // block per row. Where most of the elements are in rows of more than
 // 2^RES_LOG2, which are listed anyway, so are those of wave_max < n <=
 // 2^RES_LOG2 (4096 rows up to 2^20: 614 us listed, 631 us run by their blocks).
+// Without resident rows the single-pass rows are run here whatever the batch is
+// (listed they take another kernel, whose sums have another order): 65536 x 4096
+// 363 us, 533 listed; 200,000 up to 4096 167 us, 291 listed.
 void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeader* h) {
   const int64_t mean = elems / rows;
-  const int64_t block_max = p.resident_segments > 0 ? int64_t(1) << nrm::RES_LOG2 : 0;
-  h->run_max = block_max;
+  const int64_t block_max = int64_t(1) << nrm::RES_LOG2;
+  h->run_max = std::min(block_max, short_max_of(p));
   if (rows <= 512) {
     h->rows_per_block = 1;
   } else if (mean >= 2 * block_max) {
     h->rows_per_block = nrm::ROWS_WAVES;
-    h->run_max = 0;
+    if (p.resident_segments > 0) h->run_max = 0;
   } else {
     h->rows_per_block = mean >= 4096 ? 2 : mean >= 1536 ? 4 : mean > 512 || rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
   }

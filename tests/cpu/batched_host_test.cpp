@@ -252,6 +252,29 @@ static void test_tree_height() {
   CHECK(check_batch_params(p) == NRM_OK);
 }
 
+// Without resident rows a single-pass row of at most 2^RES_LOG2 elements is run by
+// its block in every batch (its bits must not depend on the other rows), and
+// batches of short rows are cut up as they are with resident rows.
+static void test_cuts_without_resident_rows() {
+  Ctx on, off;
+  off.bparams.resident_segments = 0;
+  for (const auto& shape : std::vector<std::pair<int, int>>{{256, 4}, {1024, 8}, {64, 1}}) {
+    off.bparams.block = shape.first;
+    off.bparams.short_regs = shape.second;
+    const int64_t run = std::min<int64_t>(shape.first * shape.second * 4, int64_t(1) << nrm::RES_LOG2);
+    for (int64_t rows : {1, 512, 513, 4096, 4097, 200000, 1 << 20})
+      for (int64_t mean : {0, 17, 256, 600, 2048, 5000, 20000, 40000, 1 << 21}) {
+        BatchHeader a, b;
+        memset(&a, 0, sizeof(a));
+        memset(&b, 0, sizeof(b));
+        cut_rows(on.bparams, rows, rows * mean, &a);
+        cut_rows(off.bparams, rows, rows * mean, &b);
+        CHECK(b.run_max == run);
+        CHECK(b.rows_per_block == a.rows_per_block);
+      }
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"rows_grid", test_rows_grid},
@@ -259,6 +282,7 @@ int main(int argc, char** argv) {
       {"failed_launch", test_failed_launch},
       {"workspace_layout", test_workspace_layout},
       {"tree_height", test_tree_height},
+      {"cuts_without_resident_rows", test_cuts_without_resident_rows},
   };
   const auto t = tests.find(argc > 1 ? argv[1] : "");
   if (t == tests.end()) {

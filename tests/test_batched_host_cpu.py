@@ -26,7 +26,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["rows_grid", "captured_tables", "failed_launch", "workspace_layout", "tree_height"])
+@pytest.mark.parametrize("case", ["rows_grid", "captured_tables", "failed_launch", "workspace_layout", "tree_height",
+                                  "cuts_without_resident_rows"])
 def test_batched_host(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
