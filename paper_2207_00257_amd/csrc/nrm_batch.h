@@ -80,7 +80,8 @@ constexpr int CNT_COUNT = CNT_SET0 + 2 * CNT_SET_STRIDE;
 struct BlockShorts {
   int64_t base, count;
 };
-constexpr int ORDERED_BLOCKS = 512;
+// (65536 rows, 32 per block: rows long enough to be listed, 4 GB and more)
+constexpr int ORDERED_BLOCKS = 2048;
 
 // One row's reduction result: the sum (a) for normalize, or the exponent and
 // the scaled sum (a = k, b = s) for softmax.

@@ -483,7 +483,7 @@ struct ListRange {
   int64_t base;
   uint32_t start, count;
 };
-static_assert(ORDERED_BLOCKS == RES_BLOCK, "one range per thread");
+static_assert(ORDERED_BLOCKS % RES_BLOCK == 0, "a whole number of ranges per thread");
 
 // Persistent blocks: the units are the long rows' tile sums, then the
 // segments of the resident rows, both taken one at a time from a counter in
@@ -523,7 +523,7 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
   const int64_t* set1 = list_counters(a, 1);
   const int64_t t0 = set0[LIST_TILES * CNT_LINE], s0 = set0[LIST_SHORT * CNT_LINE];
   const int64_t t1 = set1[LIST_TILES * CNT_LINE], s1 = set1[LIST_SHORT * CNT_LINE];
-  const BlockShorts mine = a.block_shorts[threadIdx.x];
+  const BlockShorts mine0 = a.block_shorts[threadIdx.x];
   int64_t n_long = call & 1 ? t1 : t0, n_short = call & 1 ? s1 : s0;
   // (entries past the capacity were not written; in row order they are passed
   // over one by one)
@@ -540,28 +540,43 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
   const uint32_t ep = call_tag(call);
   float* lse = lse_out(a);
   unsigned long long* stall = reinterpret_cast<unsigned long long*>(a.cnt + CNT_STALL);
-  // Small batches: the segments are taken in the rows' order, whatever the
-  // order in which the blocks of batch_rows_kernel appended them: thread t
-  // holds block t's range of the list and where it starts in row order.
-  // (4096 rows, 1.7 GB: 642 us in memory order, 666 us shuffled.)
+  // Up to ORDERED_BLOCKS blocks: the segments are taken in the rows' order,
+  // whatever the order in which the blocks of batch_rows_kernel appended them:
+  // thread t holds the ranges of the list of blocks t, t + RES_BLOCK, ... and
+  // where they start in row order. (4096 rows, 1.7 GB: 642 us in memory order, 666
+  // us shuffled; 8192 x 40000 451 and 499, 16384 x 40000 867 and 963.)
   if (ordered > 0) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t count = (int64_t)threadIdx.x < ordered ? (uint32_t)mine.count : 0u;
-    const uint32_t incl = wave_scan32(count, lane);
-    if (lane == 63) s_scan[wave] = incl;
-    lds_barrier();
-    uint32_t start = incl - count;
-    for (int w = 0; w < wave; ++w) start += s_scan[w];
-    s_range[threadIdx.x] = ListRange{mine.base, start, count};
+    uint32_t before = 0;
+    for (int k = 0; k < ordered; k += RES_BLOCK) {
+      const int64_t b = k + threadIdx.x;
+      BlockShorts mine = mine0;
+      if (k > 0) {
+        mine = b < ordered ? a.block_shorts[b] : BlockShorts{0, 0};
+        lds_barrier();  // s_scan is reused
+      }
+      const uint32_t count = b < ordered ? (uint32_t)mine.count : 0u;
+      const uint32_t incl = wave_scan32(count, lane);
+      if (lane == 63) s_scan[wave] = incl;
+      lds_barrier();
+      uint32_t start = before + incl - count;
+      for (int w = 0; w < RES_BLOCK / 64; ++w) {
+        if (w < wave) start += s_scan[w];
+        before += s_scan[w];
+      }
+      s_range[b] = ListRange{mine.base, start, count};
+    }
   }
   lds_barrier();
   int64_t u = uniform64(s_claim);
   while (u < units) {
     int64_t pos = u - n_long;  // in the list of segments
     if (pos >= 0 && ordered > 0) {
-      const ListRange r = s_range[threadIdx.x];
-      const uint32_t off = (uint32_t)pos - r.start;
-      if ((uint32_t)pos >= r.start && off < r.count) s_pos = r.base + off;
+      for (int k = 0; k < ordered; k += RES_BLOCK) {
+        const ListRange r = s_range[k + threadIdx.x];
+        const uint32_t off = (uint32_t)pos - r.start;
+        if ((uint32_t)pos >= r.start && off < r.count) s_pos = r.base + off;
+      }
       lds_barrier();
       pos = uniform64(s_pos);
     }

@@ -333,20 +333,32 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 // 8 303 us). Rows run by the block take turns in it, so long ones get a block
 // (nearly) each: 16384 x 10000 in 237 us with 2 per block, 257 us with 4, and
 // 4 log-uniform up to 65536 in 288 and 280 us; and a batch of few rows one
-// block per row. Where most of the elements are in rows of more than
-// 2^RES_LOG2, which are listed anyway, so are those of wave_max < n <=
-// 2^RES_LOG2 (4096 rows up to 2^20: 614 us listed, 631 us run by their blocks).
+// block per row.
+//
+// Where the mean row is of more than 2^RES_LOG2 elements, most are in listed
+// rows, and so are those of wave_max < n <= 2^RES_LOG2 then. The listed segments
+// are taken in row order where the batch has at most ORDERED_BLOCKS blocks: many
+// such rows go 32 per block (16384 x 20000: 475 us, 8 per block 489, run by their
+// blocks 2 at a time 590; 12000 of 32 to 2^18 482, 493 and 537; 7895 x 17000 230,
+// 235 and 276). In large batches of binary32 the same pays from three quarters of
+// that mean on (16384 rows of 32 to 2^17: 360 us listed, 404 us run; 11184 x 12000
+// 191 and 198), not in small ones (2000 x 12000: 50 and 38) nor for 2-byte inputs,
+// whose segments are half as many bytes (13421 x 10000 bfloat16: 191 and 103).
+// Below that it depends on how the lengths spread, which the host does not know
+// (32768 rows of 32 to 2^16, mean 8600: 398 listed, 447 run; 16384 x 8192: 239 and
+// 194).
 // Without resident rows the single-pass rows are run here whatever the batch is
 // (listed they take another kernel, whose sums have another order): 65536 x 4096
 // 363 us, 533 listed; 200,000 up to 4096 167 us, 291 listed.
 void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeader* h) {
   const int64_t mean = elems / rows;
   const int64_t block_max = int64_t(1) << nrm::RES_LOG2;
+  const bool large_f32 = h->mode == nrm::BATCH_CSR && h->csr_in_dt == NRM_F32 && elems >= (int64_t(1) << 26);
   h->run_max = std::min(block_max, short_max_of(p));
   if (rows <= 512) {
     h->rows_per_block = 1;
-  } else if (mean >= 2 * block_max) {
-    h->rows_per_block = nrm::ROWS_WAVES;
+  } else if (mean > block_max || (large_f32 && mean >= block_max / 4 * 3)) {
+    h->rows_per_block = rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
     if (p.resident_segments > 0) h->run_max = 0;
   } else {
     h->rows_per_block = mean >= 4096 ? 2 : mean >= 1536 ? 4 : mean > 512 || rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
