@@ -49,6 +49,16 @@ constexpr int64_t kGraphElems = int64_t(1) << 27;
 constexpr int64_t kApartElems = int64_t(1) << 26;
 constexpr int64_t kApartElemsWide = int64_t(1) << 27;  // with outputs wider than inputs among them
 
+// From 2^27 elements on a quarter of the resident limit is enough of a mean: with
+// lengths spread over a few powers of two most elements are in long rows then
+// (1000 rows of 32 to 2^22 binary32, mean 350,000: 773 and 722 us; bfloat16 499 and
+// 441), and equal rows of that mean, none of them long, do not lose by the idle
+// launches more than they gain without a replay (1000 x 300,000: 418 and 415).
+bool apart_rows(const BatchArgs& a, int64_t elems, int64_t mean, bool wide) {
+  if (!a.res_on) return false;
+  return elems >= kApartElemsWide ? mean > a.short_max / 4 : !wide && elems >= kApartElems && mean > a.short_max;
+}
+
 nrm_batch_params default_batch_params() {
   nrm_batch_params p;
   std::memset(&p, 0, sizeof(p));
@@ -415,7 +425,7 @@ int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nr
   a.header = h;
   cut_rows(c->bparams, nrows, elems, &a.header);
   BatchPlan p = plan_of(c, a.header, nrows, elems, longest, acc);
-  a.apart = a.res_on && elems >= (wide ? kApartElemsWide : kApartElems) && elems / nrows > a.short_max;
+  a.apart = apart_rows(a, elems, elems / nrows, wide);
   bool replay = c->bparams.graph && elems >= kGraphElems && !a.apart;
   bool ring = replay || table;
   if (ring) {

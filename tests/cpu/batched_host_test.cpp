@@ -156,11 +156,11 @@ static void test_captured_tables() {
       CHECK(captured[k][r].in == reinterpret_cast<const char*>(in.data() + 100 * k + r * (10 + k)));
     }
   const int launches = g_launches;
-  const std::vector<int64_t> offsets(201, 0);
-  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 200, kGraphElems, NRM_ACC_F32,
+  const std::vector<int64_t> offsets(1001, 0);
+  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 1000, kGraphElems, NRM_ACC_F32,
                                  nullptr) != NRM_OK);  // a replay: no graph can be made here
   g_capturing = true;
-  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 200, kGraphElems, NRM_ACC_F32,
+  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 1000, kGraphElems, NRM_ACC_F32,
                                  nullptr) == NRM_OK);
   g_capturing = false;
   CHECK(g_launches == launches + 1 && g_args.header.offsets == offsets.data());
@@ -275,6 +275,34 @@ static void test_cuts_without_resident_rows() {
   }
 }
 
+// Which batches run their long rows in launches of their own: never without
+// resident rows, never a small batch or one of short rows, and then not as a replay.
+static void test_apart_rule() {
+  Ctx c;
+  std::vector<float> in(16);
+  const std::vector<int64_t> offsets(100001, 0);
+  auto apart = [&](int64_t rows, int64_t capacity, int in_dt, int out_dt) {
+    const int64_t half = int64_t(1) << 45;  // addresses only: nothing is read here
+    void* from = reinterpret_cast<void*>(half);
+    void* to = reinterpret_cast<void*>(half + half / 2);
+    return nrm_normalize_batched_ex(&c, to, out_dt, from, in_dt, offsets.data(), rows, capacity, NRM_ACC_F32, nullptr) ==
+               NRM_OK && g_args.apart;
+  };
+  const int64_t b = kApartElems, w = kApartElemsWide;
+  c.bparams.graph = 0;
+  CHECK(!apart(63, b - 1, NRM_F32, NRM_F32) && apart(63, b, NRM_F32, NRM_F32) && apart(63, b, NRM_BF16, NRM_BF16));
+  CHECK(!apart(64, b, NRM_F32, NRM_F32));  // mean 2^20
+  CHECK(apart(1, b, NRM_F32, NRM_BF16) && !apart(1, b, NRM_BF16, NRM_F32) && !apart(1, w - 1, NRM_F16, NRM_F32));
+  CHECK(apart(1, w, NRM_BF16, NRM_F32));
+  CHECK(apart(511, w, NRM_F32, NRM_F32) && !apart(512, w, NRM_F32, NRM_F32));  // mean 2^18
+  c.bparams.resident_segments = 0;
+  CHECK(!apart(1, w, NRM_F32, NRM_F32));
+  c.bparams.resident_segments = 64;
+  c.bparams.graph = 1;  // a replay fails here
+  CHECK(apart(1, w, NRM_F32, NRM_F32));
+  CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 512, w, NRM_ACC_F32, nullptr) != NRM_OK);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"rows_grid", test_rows_grid},
@@ -282,6 +310,7 @@ int main(int argc, char** argv) {
       {"failed_launch", test_failed_launch},
       {"workspace_layout", test_workspace_layout},
       {"tree_height", test_tree_height},
+      {"apart_rule", test_apart_rule},
       {"cuts_without_resident_rows", test_cuts_without_resident_rows},
   };
   const auto t = tests.find(argc > 1 ? argv[1] : "");
