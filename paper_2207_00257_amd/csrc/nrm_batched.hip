@@ -824,7 +824,7 @@ hipError_t phase2_acc(const BatchPlan& p, const BatchArgs& a, hipStream_t s) {
 // non-temporally, the others temporally, since the neighbour's wavefront finds
 // the shared line in the L2. (2^20 rows of 250 binary32: 475 us non-temporal,
 // 371 us temporal; 200,000 rows of up to 4096: 187 and 177 us; 2^17 rows of
-// 2048, whole lines: 369 us non-temporal, 397 us temporal.)
+// 2048, whole lines, at 4 per block: 369 us non-temporal, 397 us temporal.)
 template <int DT>
 __device__ __forceinline__ bool whole_lines(const char* p, int n) {
   return (((uint32_t)reinterpret_cast<uintptr_t>(p) | (uint32_t)(n * Elem<DT>::SIZE)) & (BODY_ALIGN - 1)) == 0;
@@ -1021,8 +1021,10 @@ __device__ __forceinline__ void dispatch_quarter(const RowDesc& d, float* lse) {
 // wavefront may hold four of them and its neighbour none. For that the block's
 // barrier stands before the rows there (200,000 rows of up to 4096: 163 us, 175
 // with own rows only; 2^20 rows of 17: 118 and 138; 2^20 of 256: 346 and 353);
-// with one row each it stands behind them (100,000 rows of 100 to 3000: 149 us,
-// before them 159 to 176; rows of 2048 alone are the other way: 393 and 356).
+// with one row each it stands behind them (8 rows per block, 100,000 rows of 100
+// to 3000: 149 us, before them 160; 2^17 rows of 2048: 356 either way. Blocks that
+// rows of that length do not fill lose by it, 4 per block 398 and 355 us, but such
+// blocks are left to longer rows, which the block runs: 65536 x 3000 290 either way).
 // It then appends its rows of more than run_max elements to the lists:
 // the segments of a resident row (one for a row of at most 2^RES_LOG2 elements;
 // resident rows off, a single-pass row's one entry) to `shorts`, a long row's

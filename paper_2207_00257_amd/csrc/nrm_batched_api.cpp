@@ -338,12 +338,16 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 // How batch_rows_kernel is cut up; the results are the same. A wavefront costs
 // the dispatcher about 0.4 ns, so many short rows go four to a wavefront (2^20
 // rows of 64 binary32: 159 us with 32 rows per block, 489 us with 8). Rows of
-// several hundred elements take a wavefront each, one after the other: 8 per
-// block (2^18 x 1000: 350 us, with 32 377 us; 65536 x 3000: 4 per block 293 us,
-// 8 303 us). Rows run by the block take turns in it, so long ones get a block
-// (nearly) each: 16384 x 10000 in 237 us with 2 per block, 257 us with 4, and
-// 4 log-uniform up to 65536 in 288 and 280 us; and a batch of few rows one
-// block per row.
+// several hundred elements, up to about the longest that a wavefront takes, get
+// one each: 8 per block (2^18 x 1000: 350 us, with 32 377 us; 65536 x 1536 133 us, 4
+// per block 170; 2^17 x 2048 bfloat16 177 and 244; of binary32 of that length those
+// in whole lines gain, 2^17 x 2048 365 and 402, others lose, 2^17 x 2000 387 and
+// 374, and keep 4 per block). Longer rows are run by
+// the block and take turns in it: 4 per block (65536 x 3000 290 us, 8 per block
+// 299), and from 4096 elements on nearly a block each: 16384 x 10000 in 237 us
+// with 2 per block, 257 us with 4, and 4 log-uniform up to 65536 in 288 and 280 us
+// (2-byte inputs would keep 8 per block up to 4096 elements: 32768 x 4096 bfloat16
+// 140 us, 2 per block 156); and a batch of few rows one block per row.
 //
 // Where the mean row is of more than 2^RES_LOG2 elements, most are in listed
 // rows, and so are those of wave_max < n <= 2^RES_LOG2 then. The listed segments
@@ -364,6 +368,8 @@ void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeade
   const int64_t mean = elems / rows;
   const int64_t block_max = int64_t(1) << nrm::RES_LOG2;
   const bool large_f32 = h->mode == nrm::BATCH_CSR && h->csr_in_dt == NRM_F32 && elems >= (int64_t(1) << 26);
+  const int64_t wave_mean = h->mode == nrm::BATCH_CSR && nrm::dtype_size(h->csr_in_dt) == 2 ? nrm::WAVE_MAX_ELEMS
+                                                                                        : nrm::WAVE_MAX_ELEMS / 8 * 7;
   h->run_max = std::min(block_max, short_max_of(p));
   if (rows <= 512) {
     h->rows_per_block = 1;
@@ -371,7 +377,10 @@ void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeade
     h->rows_per_block = rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
     if (p.resident_segments > 0) h->run_max = 0;
   } else {
-    h->rows_per_block = mean >= 4096 ? 2 : mean >= 1536 ? 4 : mean > 512 || rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
+    h->rows_per_block = mean >= 4096                 ? 2
+                        : mean > wave_mean           ? 4
+                        : mean > 512 || rows <= 4096 ? nrm::ROWS_WAVES
+                                                     : nrm::ROWS_MAX;
   }
   h->grid_x = nrm::rows_grid_x(ceil_div(rows, h->rows_per_block));
 }

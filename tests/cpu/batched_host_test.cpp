@@ -303,6 +303,21 @@ static void test_apart_rule() {
   CHECK(nrm_normalize_batched_ex(&c, in.data(), NRM_F32, in.data(), NRM_F32, offsets.data(), 512, w, NRM_ACC_F32, nullptr) != NRM_OK);
 }
 
+// A block's eight wavefronts have a row each while the mean row is about one
+// wavefront's.
+static void test_cuts_of_wavefront_rows() {
+  Ctx c;
+  for (int dt : {NRM_F32, NRM_BF16, NRM_F16})
+    for (int64_t rows : {5000, 1 << 17})
+      for (int64_t mean : {513, 1000, 1536, 1792, 1793, 2000, 2048, 2049, 3000}) {
+        BatchHeader h;
+        memset(&h, 0, sizeof(h));
+        h.csr_in_dt = dt;
+        cut_rows(c.bparams, rows, rows * mean, &h);
+        CHECK(h.rows_per_block == (mean <= (dt == NRM_F32 ? 1792 : 2048) ? nrm::ROWS_WAVES : 4));
+      }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> tests = {
       {"rows_grid", test_rows_grid},
@@ -311,6 +326,7 @@ int main(int argc, char** argv) {
       {"workspace_layout", test_workspace_layout},
       {"tree_height", test_tree_height},
       {"apart_rule", test_apart_rule},
+      {"cuts_of_wavefront_rows", test_cuts_of_wavefront_rows},
       {"cuts_without_resident_rows", test_cuts_without_resident_rows},
   };
   const auto t = tests.find(argc > 1 ? argv[1] : "");
