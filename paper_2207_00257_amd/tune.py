@@ -180,14 +180,63 @@ def sweep(n: int, in_dtype="f32", out_dtype="f32", accum="f32", reps=5, quick=Fa
     return best, rt, mt, table
 
 
+def resident_candidates(base, cus, quick=False):
+    """How many segments a row may have to be held on chip (0: none), and the
+    persistent blocks, one to three per CU (more do not fit)."""
+    for segs in ((0, 64) if quick else (0, 16, 32, 64)):
+        for per_cu in ((2, 3) if quick else (1, 1.5, 2, 3)):
+            yield dict(base, resident_segments=segs, resident_grid=max(segs, int(cus * per_cu)))
+
+
+def wave_candidates(base, quick=False):
+    """The longest row of one wavefront (0: none)."""
+    for wmax in ((0, 2048) if quick else (0, 256, 1024, 2048)):
+        yield dict(base, wave_max=wmax)
+
+
+def tile_candidates(base, cus, longest, quick=False):
+    """The tiles' shapes, as far as a batch with rows of up to `longest`
+    elements can show them: without resident rows those of the three launches,
+    with them the tile size, if any row is long."""
+    logs = (14, 15, 16) if quick else (13, 14, 15, 16, 17)
+    if base["resident_segments"] > 0:
+        if longest > base["resident_segments"] << 14:
+            for tile_log2 in logs:
+                yield dict(base, tile_log2=tile_log2)
+        return
+    for block in (256, 512, 1024):
+        for unroll in ((2, 4) if quick else (1, 2, 4, 8)):
+            for tile_log2 in logs:
+                for short_regs in ((2, 8) if quick else (1, 2, 4, 8)):
+                    for gmul in ((2, 4) if quick else (1, 2, 4, 8)):
+                        yield dict(base, block=block, unroll=unroll, tile_log2=tile_log2, short_regs=short_regs,
+                                   grid=cus * gmul * max(1, 1024 // block))
+
+
+def map_candidates(base, cus):
+    """The divide's launch, without resident rows."""
+    if base["resident_segments"] > 0:
+        return
+    for map_block in (256, 512, 1024):
+        for map_unroll in (1, 2, 4, 8):
+            for gmul in (1, 2, 4, 8, 16, 32):
+                yield dict(base, map_block=map_block, map_unroll=map_unroll,
+                           map_grid=cus * gmul * max(1, 1024 // map_block))
+
+
+def keep_candidates(base, longest):
+    """The temporal tail that the tile sums leave in the last-level cache."""
+    if base["resident_segments"] == 0 or longest > base["resident_segments"] << 14:
+        for keep in (0, 64, 128, 192, 224, 256, 288):
+            yield dict(base, keep_mib=keep)
+
+
 def sweep_batched(rows=4096, seed=4, reps=3, quick=False, log=print):
     """Sweep the batched path's launch shape on the ragged workload (rows with
     log-uniform lengths in [32, 2^20], LogNormal(0,1) FP32), timing whole
-    calls (the rows, then the lists of the longer ones) with the
-    library's events: first the resident rows' limit and grid, then the
-    short rows' (one per wavefront) limit and grid, then, when some row of
-    the workload is longer than the resident limit, the tile phases'
-    shapes."""
+    calls (the rows, then the lists of the longer ones) with the library's
+    events: first the resident rows' limit and grid, then the longest row of
+    one wavefront, then what shapes the tiles in the form chosen so far."""
     import torch
 
     from . import api, synth
@@ -199,9 +248,10 @@ def sweep_batched(rows=4096, seed=4, reps=3, quick=False, log=print):
     offs_d = torch.from_numpy(offs).to(dev)
     ctx = api.Context()
     cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    longest = int((offs[1:] - offs[:-1]).max())
     base_p = ctx.get_batch_params()
     base_p["graph"] = 1
-    table, best, best_t = [], None, float("inf")
+    table, best, best_t = [], base_p, float("inf")
     t0 = time.time()
     ctx.batch_reserve(rows, x.size)
 
@@ -218,71 +268,18 @@ def sweep_batched(rows=4096, seed=4, reps=3, quick=False, log=print):
         ctx.set_timing(False)
         return t / c
 
-    # resident rows first: how many segments a row may have to be held on
-    # chip (0: none, every row takes the tile phases), and how many blocks
-    for segs in ((0, 64) if quick else (0, 16, 32, 64)):
-        for gmul in ((2,) if quick else (1, 1.5, 2)):
-            p = dict(base_p, resident_segments=segs, resident_grid=max(segs, int(cus * gmul)))
+    for stage in (lambda: resident_candidates(best, cus, quick), lambda: wave_candidates(best, quick),
+                  lambda: tile_candidates(best, cus, longest, quick), lambda: map_candidates(best, cus),
+                  lambda: keep_candidates(best, longest)):
+        n = len(table)
+        for p in list(stage()):
             ms = measure(p)
             if ms is None:
                 continue
             table.append({"kernel": "batched", "params": p, "ms": ms})
             if ms < best_t:
                 best, best_t = p, ms
-    # rows per wavefront: rows up to wave_max elements one per wavefront (0:
-    # none), and that kernel's grid
-    for wmax in ((0, 2048) if quick else (0, 256, 1024, 2048)):
-        for gmul in ((4,) if quick or wmax == 0 else (2, 4, 8)):
-            p = dict(best, wave_max=wmax, wave_grid=cus * gmul)
-            ms = measure(p)
-            if ms is None:
-                continue
-            table.append({"kernel": "batched", "params": p, "ms": ms})
-            if ms < best_t:
-                best, best_t = p, ms
-    base_p = dict(best)
-    # the tile phases' shapes matter only for rows longer than the resident
-    # limit; with every row of the workload resident they are not swept
-    longest = int((offs[1:] - offs[:-1]).max())
-    all_resident = base_p["resident_segments"] << 14 >= longest
-    if all_resident:
-        log("every row is resident (longest %d): tile phases not swept" % longest)
-    stage1 = []
-    if not all_resident:
-        for block in (256, 512, 1024):
-            for unroll in ((2, 4) if quick else (1, 2, 4, 8)):
-                for tile_log2 in ((14, 15, 16) if quick else (13, 14, 15, 16, 17)):
-                    for short_regs in ((2, 8) if quick else (1, 2, 4, 8)):
-                        for gmul in ((2, 4) if quick else (1, 2, 4, 8)):
-                            stage1.append(dict(base_p, block=block, unroll=unroll, tile_log2=tile_log2,
-                                               short_regs=short_regs, grid=cus * gmul * max(1, 1024 // block)))
-    for p in stage1:
-        ms = measure(p)
-        if ms is None:
-            continue
-        table.append({"kernel": "batched", "params": p, "ms": ms})
-        if ms < best_t:
-            best, best_t = p, ms
-    for map_block in ((256, 512, 1024) if not all_resident else ()):
-        for map_unroll in (1, 2, 4, 8):
-            for gmul in (1, 2, 4, 8, 16, 32):
-                p = dict(best, map_block=map_block, map_unroll=map_unroll,
-                         map_grid=cus * gmul * max(1, 1024 // map_block))
-                ms = measure(p)
-                if ms is None:
-                    continue
-                table.append({"kernel": "batched", "params": p, "ms": ms})
-                if ms < best_t:
-                    best, best_t = p, ms
-    # the temporal tail phase 1 leaves in the last-level cache for phase 2
-    for keep in ((0, 64, 128, 192, 224, 256, 288) if not all_resident else ()):
-        p = dict(best, keep_mib=keep)
-        ms = measure(p)
-        if ms is None:
-            continue
-        table.append({"kernel": "batched", "params": p, "ms": ms})
-        if ms < best_t:
-            best, best_t = p, ms
+        log("  %d candidates, best %.4f ms" % (len(table) - n, best_t), flush=True)
     # the leaders again, interleaved round by round with more repetitions
     leaders = []
     for r in sorted(table, key=lambda r: r["ms"]):
@@ -304,9 +301,17 @@ def sweep_batched(rows=4096, seed=4, reps=3, quick=False, log=print):
     return best, best_t, table
 
 
+def serve_candidates(cus, quick=False):
+    """What shapes a serving group's batched call: the persistent blocks, the
+    longest row of one wavefront, the tiles of the rows beyond 2^20."""
+    space = itertools.product((1, 2, 3), (1024, 2048), (14, 15, 16))
+    out = [dict(resident_grid=cus * per_cu, wave_max=wmax, tile_log2=tile_log2, graph=1) for per_cu, wmax, tile_log2 in space]
+    return out[::4] if quick else out
+
+
 def sweep_serve(quick=False, log=print):
     """Sweep the batched launch shape for the serving workload: the server
-    (4 slots, spreading, graph replay) replays open-loop Poisson traces at
+    (4 slots, spreading) replays open-loop Poisson traces at
     100k and 200k requests/s (n log-uniform in [2^8, 2^24], 70 % FP32 / 30 %
     BF16); a candidate's score is the sum of the two p99 latencies."""
     import numpy as np
@@ -315,20 +320,16 @@ def sweep_serve(quick=False, log=print):
     from . import serve
 
     torch.cuda.init()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
     pool = serve.InputPool(1 << 24, 7)
     traces = []
     for rate in (100000.0, 200000.0):
         tr = serve.make_trace(rate, 1.2, seed=9)
         traces.append((tr, pool.pointers(tr["in_dt"], pool.offsets(tr["n"], 10))))
-    shapes = [(256, 8, 4), (1024, 2, 2)]
-    space = list(itertools.product(shapes, (1024, 2048), (512, 1024, 2048), (2, 4)))
-    if quick:
-        space = space[:4]
+    space = serve_candidates(cus, quick)
     table, best, best_s = [], None, float("inf")
     t0 = time.time()
-    for (block, unroll, map_unroll), grid, map_grid, short_regs in space:
-        bp = dict(block=block, unroll=unroll, map_unroll=map_unroll, grid=grid, tile_log2=15,
-                  short_regs=short_regs, map_block=1024, map_grid=map_grid, graph=1)
+    for bp in space:
         p99 = []
         for tr, pt in traces:
             srv = serve.Server(slots=4, batching=True, batch_params=bp)
@@ -339,7 +340,7 @@ def sweep_serve(quick=False, log=print):
             p99.append(serve.latency_stats([c for c in comps if c[2] - t_start >= int(0.2e9)])["p99_ms"])
         score = sum(p99)
         table.append({"params": bp, "p99_ms": p99, "score": score})
-        log("  %s p99 %.3f / %.3f ms" % ({k: bp[k] for k in ("block", "grid", "map_grid", "short_regs")}, p99[0], p99[1]))
+        log("  %s p99 %.3f / %.3f ms" % (bp, p99[0], p99[1]), flush=True)
         if score < best_s:
             best, best_s = bp, score
     log("serve sweep: %d candidates in %.1f s, best p99 sum %.3f ms %s" % (len(space), time.time() - t0, best_s, best))
