@@ -720,7 +720,7 @@ def bench_nll(args, n=1 << 22, c=1000):
     torch_ms = timed(lambda: F.nll_loss(logp, target, weight=weight, reduction="mean"))
     kept = int(idx.numel())
     alg_gbs = 12.0 * n / (ms * 1e-3) / 1e9
-    sector_gbs = (8.0 * n + 64.0 * kept) / (ms * 1e-3) / 1e9
+    sector_gbs = (8.0 * n + 128.0 * kept) / (ms * 1e-3) / 1e9
     line = {
         "metric": METRIC, "value": round(n / (ms * 1e-3), 1), "unit": "samples/s",
         "algorithmic_GBps": round(alg_gbs, 2), "sector_model_GBps": round(sector_gbs, 2),
@@ -729,7 +729,7 @@ def bench_nll(args, n=1 << 22, c=1000):
         "config": {"workload": "forward NLL loss, mean, class weights: N = 2^22 samples, C = 1000 classes, "
                                "logp = -Exponential(mean 3) FP32 [N, C], int64 targets (5 %% ignored), weights "
                                "U[0.5, 1.5); device-side seeded draw; models 12 B/sample algorithmic, 8 B + one "
-                               "64-byte sector per kept sample", "n": n, "classes": c},
+                               "128-byte line per kept sample", "n": n, "classes": c},
         "torch_nll_loss_ms": round(torch_ms, 5),
         "rel_err_vs_binary64": abs(got - ref) / ref,
     }

@@ -145,7 +145,7 @@ inline int64_t rows_grid_y(int64_t blocks) { return (blocks + ROWS_GRID_X - 1) /
 inline int64_t rows_grid_x(int64_t blocks) { return (blocks + rows_grid_y(blocks) - 1) / rows_grid_y(blocks); }
 
 // Elements of one resident segment: 512 threads x 8 vectors of 4 binary32
-// (4 vectors of 8 for 2-byte inputs); two blocks fit a CU's registers.
+// (4 vectors of 8 for 2-byte inputs); three blocks fit a CU's registers.
 constexpr int RES_LOG2 = 14;
 constexpr int RES_BLOCK = 512;
 constexpr int RES_MAX_SEGMENTS = 64;  // one wavefront lane per segment in the merge

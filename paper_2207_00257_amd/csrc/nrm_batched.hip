@@ -3,11 +3,11 @@
 // of the element-wise divide exactly as in the plain path (arXiv 2207.00257,
 // Fig. 1 and Sec. IV-C), in two launches for the batch.
 //
-//   batch_rows_kernel    a grid over the rows themselves (8 or 32 consecutive
+//   batch_rows_kernel    a grid over the rows themselves (1 to 32 consecutive
 //                        rows per block, in dispatch order): resolves and
 //                        validates each row (from CSR offsets or a descriptor
 //                        table) and runs the rows of at most 2^14 elements on
-//                        the spot: up to 512 elements on 16 lanes, up to
+//                        the spot: up to 256 elements on 16 lanes, up to
 //                        wave_max (2048) on one wavefront, the rest on the
 //                        block, each read into registers, summed, divided and
 //                        written. The longer rows are appended to two work
@@ -495,13 +495,15 @@ static_assert(ORDERED_BLOCKS % RES_BLOCK == 0, "a whole number of ranges per thr
 // like the resident rows'.
 //
 // HBM bounds it: resident rows move 8 bytes per binary32 element, long rows
-// 12. 4096 rows of up to 2^20 binary32 (3.43 GB) take 572 us per call with three
-// blocks per CU (80 registers; with the plain reduce's 16 chains in the tile
-// sums 128 and two blocks, 616 us; four blocks spilled: 597-622 us), BF16 ones
-// 404 against 478 us, the latency of their smaller segments (claim, entry,
-// elements, exchange) not hidden. The tiles of the divide are dealt statically because nothing waits for
-// them, and in units of 2^13 elements so that the last round of 512 blocks is
-// short (whole tiles of 2^15 left up to half of the blocks idle in it).
+// 12. 4096 rows of up to 2^20 binary32 (3.43 GB) take 577 us per call launched
+// directly (587 replayed) with three blocks per CU (80 registers; with the plain
+// reduce's 16 chains in the tile sums 128 and two blocks, 616 us; four blocks
+// spilled: 597-622 us), BF16 ones 404 against 478 us, the latency of their smaller
+// segments (claim, entry, elements, exchange) not hidden. The tiles of the divide
+// are dealt statically because nothing waits for them, and in units of 2^13
+// elements so that the last round of 512 blocks is short (whole tiles of 2^15
+// left up to half of the blocks idle in it). Large batches of long rows are
+// faster apart (below).
 template <int ACC>
 __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(6, 6))) batch_resident_kernel(BatchArgs a) {
   __shared__ Acc<ACC> slots[MAX_WAVES];
@@ -1033,8 +1035,8 @@ __device__ __forceinline__ void dispatch_quarter(const RowDesc& d, float* lse) {
 // run_max one after the other.
 //
 // What bounds it: with many short rows HBM (2^20 rows of 256 binary32, 2.16 GB:
-// 346 us per call, 6.2 TB/s, against 564 us in six launches over planned
-// tables), with few the launch and the chain of dependent loads (offsets,
+// 348 us per call launched directly, 6.2 TB/s, 358 replayed, against 572 us in six
+// launches over planned tables), with few the launch and the chain of dependent loads (offsets,
 // elements; 64 rows of up to 256: 4.1 us per call). 80 registers, three blocks
 // per CU: spilling any of them cost more than a block less (2^20 rows of 256:
 // 361 us with none, 523 us with 29).

@@ -30,10 +30,12 @@ constexpr size_t kSmallBytes = kErrorOffset + 128;
 int64_t align_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
 // Batches of at least this many elements are replayed from a captured graph
-// (parameter graph = 1); smaller ones are launched kernel by kernel. On MI355X
+// (parameter graph = 1), smaller ones launched kernel by kernel. On MI355X
 // hipGraphLaunch takes 15.8 us of the host whatever the graph holds, a kernel
-// launch 1.1 us: a replay is hidden only behind a call that runs longer than
-// that on the device (2^24 binary32 elements read and written: about 21 us).
+// launch 1.1 us, and a replay of the two launches about 10 us more of the device
+// than the launches themselves (4096 rows of up to 2^20: 587 and 577 us; 2^20 x 256:
+// 358 and 348). No size was found where a replay is the faster one; it is kept where
+// it costs 3 % at most, for callers that ask for one submission per batch.
 constexpr int64_t kGraphElems = int64_t(1) << 27;
 
 // Batches of at least this many elements, most of them in long rows, run the
@@ -79,9 +81,9 @@ nrm_batch_params default_batch_params() {
   // their read and their write; three 512-thread blocks per CU
   p.resident_segments = 64;
   p.resident_grid = 768;
-  // rows of up to 2048 elements one per wavefront, 16 wavefronts per CU
+  // rows of up to 2048 elements one per wavefront
   p.wave_max = 2048;
-  p.wave_grid = 1024;
+  p.wave_grid = 1024;  // without effect
   return p;
 }
 
