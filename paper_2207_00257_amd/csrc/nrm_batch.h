@@ -96,7 +96,7 @@ struct BatchArgs {
   Item* tiles;           // [cap_items]: the long rows' tiles
   Item* shorts;          // [cap_items]: the resident rows' segments, or the single-pass rows
   BlockShorts* block_shorts;  // [ORDERED_BLOCKS]
-  int64_t* lrow_first;   // [cap_rows]: the first entry of each long row (resident rows off)
+  int64_t* lrow_first;   // [cap_rows]: each long row's first entry, -1: it did not fit (resident rows off, or apart)
   int64_t* cnt;          // [CNT_COUNT]
   int* error;            // [1]
   int64_t cap_rows;

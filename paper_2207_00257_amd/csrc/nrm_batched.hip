@@ -678,6 +678,7 @@ __global__ void __launch_bounds__(RES_BLOCK) batch_tile_totals_kernel(BatchArgs 
   float* lse = lse_out(a);
   for (int64_t k = blockIdx.x; k < n_rows; k += gridDim.x) {
     const int64_t first = a.lrow_first[k];
+    if (first < 0) continue;  // the row did not fit the list
     const Item it = uniform_item(a.tiles[first]);
     const ResExchange x{a.tile_tagged + 2 * first, nullptr, nullptr, call_tag(call), a.error,
                         reinterpret_cast<unsigned long long*>(a.cnt + CNT_STALL)};
@@ -738,6 +739,7 @@ __global__ void __launch_bounds__(1024) batch_rowsum_kernel(BatchArgs a) {
   const Acc<ACC>* part = static_cast<const Acc<ACC>*>(a.partials);
   for (int64_t k = blockIdx.x; k < n_lrows; k += gridDim.x) {
     const int64_t first = a.lrow_first[k];
+    if (first < 0) continue;  // the row did not fit the list
     const int32_t row = a.tiles[first].row;
     const int64_t count = (a.tiles[first].d.n + a.tile - 1) >> a.tile_log2;
     Acc<ACC> tot = combine_partials<ACC>(part + first, count, tree, tiles);
@@ -1046,7 +1048,7 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
   __shared__ RowRes s_bcast;
   __shared__ RowDesc s_rows[ROWS_MAX];   // by the row's place in the block
   __shared__ uint32_t s_at[ROWS_MAX];    // each listed row's first entry after the block's base
-  __shared__ int64_t s_base_tiles, s_base_shorts;
+  __shared__ int64_t s_base_tiles, s_base_shorts, s_base_lrows;
   const BatchHeader& h = a.header;
   const int t = threadIdx.x, lane = t & 63, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -1102,6 +1104,8 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
   const uint32_t kept = (uint32_t)__ballot(n > 0), list = (uint32_t)__ballot(n > h.run_max);
   if (list) {
     const int64_t call = a.cnt[CNT_CALL] + 1;
+    // where kernels of their own take the long rows, these are listed too
+    const uint32_t longs = !a.res_on || a.apart ? (uint32_t)__ballot(n > h.run_max && n > a.short_max) : 0u;
     if (wave == 0) {
       const bool listed = n > h.run_max, is_long = listed && n > a.short_max;
       const uint32_t tiles = is_long ? (uint32_t)long_tiles(n, a.short_max, a.tile_log2) : 0u;
@@ -1117,6 +1121,10 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
         if (is)
           bs = __hip_atomic_fetch_add(lists + LIST_SHORT * CNT_LINE, (unsigned long long)is, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
+        if (longs)
+          s_base_lrows = (int64_t)__hip_atomic_fetch_add(lists + LIST_LONG_ROWS * CNT_LINE,
+                                                         (unsigned long long)__popc(longs), __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT);
         s_base_tiles = (int64_t)bt;
         s_base_shorts = (int64_t)bs;
         if (block < ORDERED_BLOCKS) a.block_shorts[block] = BlockShorts{(int64_t)bs, (int64_t)is};
@@ -1141,13 +1149,8 @@ __global__ void __launch_bounds__(ROWS_BLOCK) __attribute__((amdgpu_waves_per_eu
       for (int64_t i = lane; i < count && first + i < a.cap_items; i += 64)
         to[first + i] = Item{x, fits ? row : -1, (int32_t)i};
       if (lane == 0) {
-        if (!fits) {
-          atomicOr(a.error, NRM_DEVERR_CAPACITY);
-        } else if (is_long && (!a.res_on || a.apart)) {
-          unsigned long long* lists = reinterpret_cast<unsigned long long*>(list_counters(a, call));
-          a.lrow_first[__hip_atomic_fetch_add(lists + LIST_LONG_ROWS * CNT_LINE, 1ull, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT)] = first;
-        }
+        if (!fits) atomicOr(a.error, NRM_DEVERR_CAPACITY);
+        if (longs >> j & 1) a.lrow_first[s_base_lrows + __popc(longs & ((1u << j) - 1))] = fits ? first : -1;
       }
     }
   } else if (t == 0 && block < ORDERED_BLOCKS) {
