@@ -275,6 +275,11 @@ BatchArgs args_of(const nrm_ctx* c) {
   return a;
 }
 
+// Whether a batch's listed rows are mostly of one segment each.
+bool single_segments(const nrm_batch_params& q, const BatchHeader& h, int64_t mean) {
+  return q.resident_segments > 0 && h.run_max == 0 && mean <= int64_t(1) << nrm::RES_LOG2;
+}
+
 // The plan of a batch of `rows` rows of at most `elems` elements, the longest
 // at most `longest`, cut up as `h` says.
 BatchPlan plan_of(const nrm_ctx* c, const BatchHeader& h, int64_t rows, int64_t elems, int64_t longest, int acc) {
@@ -290,7 +295,11 @@ BatchPlan plan_of(const nrm_ctx* c, const BatchHeader& h, int64_t rows, int64_t 
   p.res_grid = std::min<int64_t>(q.resident_grid, (h.run_max > 0 ? 0 : rows) + 2 * (elems >> nrm::RES_LOG2) + 1);
   // long rows stream better from two blocks per CU (2^26 binary32 in one row:
   // 145 against 148 us; 16 rows of up to 2^24: 64.3 and 66.8 us)
-  if (elems / rows > short_max_of(q)) p.res_grid = std::min<int64_t>(p.res_grid, std::max(512, q.resident_segments));
+  // and so do listed rows that are single segments, which wait for nothing (30000
+  // x 16000: 614 and 660 us; 16000 x 16384 343 and 369; rows of more segments want
+  // three, 20000 x 20000 643 and 580)
+  if (elems / rows > short_max_of(q) || single_segments(q, h, elems / rows))
+    p.res_grid = std::min<int64_t>(p.res_grid, std::max(512, q.resident_segments));
   p.block = q.block;
   p.unroll = q.unroll;
   p.map_unroll = q.map_unroll;
@@ -356,10 +365,11 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 // are taken in row order where the batch has at most ORDERED_BLOCKS blocks: many
 // such rows go 32 per block (16384 x 20000: 475 us, 8 per block 489, run by their
 // blocks 2 at a time 590; 12000 of 32 to 2^18 482, 493 and 537; 7895 x 17000 230,
-// 235 and 276). In large batches of binary32 the same pays from three quarters of
-// that mean on (16384 rows of 32 to 2^17: 360 us listed, 404 us run; 11184 x 12000
-// 191 and 198), not in small ones (2000 x 12000: 50 and 38) nor for 2-byte inputs,
-// whose segments are half as many bytes (13421 x 10000 bfloat16: 191 and 103).
+// 235 and 276). In large batches of binary32 in and out the same pays from three
+// quarters of that mean on (16384 rows of 32 to 2^17: 372 us listed, 404 us run;
+// 39431 x 13074 647 and 755), not in small ones (2000 x 12000: 50 and 38) nor where
+// a segment is fewer bytes (10000 x 13074 to bfloat16: 165 and 138; 13421 x 10000
+// bfloat16: 191 and 103).
 // Below that it depends on how the lengths spread, which the host does not know
 // (32768 rows of 32 to 2^16, mean 8600: 398 listed, 447 run; 16384 x 8192: 239 and
 // 194).
@@ -369,7 +379,8 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeader* h) {
   const int64_t mean = elems / rows;
   const int64_t block_max = int64_t(1) << nrm::RES_LOG2;
-  const bool large_f32 = h->mode == nrm::BATCH_CSR && h->csr_in_dt == NRM_F32 && elems >= (int64_t(1) << 26);
+  const bool large_f32 = h->mode == nrm::BATCH_CSR && h->csr_in_dt == NRM_F32 && h->csr_out_dt == NRM_F32 &&
+                         elems >= (int64_t(1) << 26);
   const int64_t wave_mean = h->mode == nrm::BATCH_CSR && nrm::dtype_size(h->csr_in_dt) == 2 ? nrm::WAVE_MAX_ELEMS
                                                                                         : nrm::WAVE_MAX_ELEMS / 8 * 7;
   h->run_max = std::min(block_max, short_max_of(p));
@@ -437,7 +448,9 @@ int run_batch(nrm_ctx* c, const BatchHeader& h, const nrm_row* table, int64_t nr
   cut_rows(c->bparams, nrows, elems, &a.header);
   BatchPlan p = plan_of(c, a.header, nrows, elems, longest, acc);
   a.apart = apart_rows(a, elems, elems / nrows, wide);
-  bool replay = c->bparams.graph && elems >= kGraphElems && !a.apart;
+  // (a replay has the persistent blocks that it was captured with)
+  bool replay = c->bparams.graph && elems >= kGraphElems && !a.apart &&
+                !single_segments(c->bparams, a.header, elems / nrows);
   bool ring = replay || table;
   if (ring) {
     hipStreamCaptureStatus state = hipStreamCaptureStatusNone;

@@ -252,6 +252,30 @@ static void test_tree_height() {
   CHECK(check_batch_params(p) == NRM_OK);
 }
 
+// Rows of about a segment are listed in large batches of binary32 in and out, on
+// two blocks per CU and without a replay; elsewhere they are run by their blocks.
+static void test_cuts_of_one_segment_rows() {
+  Ctx c;
+  const std::vector<int64_t> offsets(40001, 0);
+  auto cut = [&](int64_t rows, int64_t mean, int in_dt, int out_dt) {
+    const int64_t half = int64_t(1) << 45;  // addresses only: nothing is read here
+    CHECK(nrm_normalize_batched_ex(&c, reinterpret_cast<void*>(half + half / 2), out_dt, reinterpret_cast<void*>(half), in_dt,
+                                   offsets.data(), rows, rows * mean, NRM_ACC_F32, nullptr) == NRM_OK);
+    return g_args.header.run_max == 0;
+  };
+  for (int64_t mean : {12288, 13074, 16384}) {
+    CHECK(cut(40000, mean, NRM_F32, NRM_F32) && g_args.header.rows_per_block == nrm::ROWS_MAX && g_plan.res_grid == 512);
+    CHECK(cut(5462, mean, NRM_F32, NRM_F32) && g_plan.res_grid == 512);
+    c.bparams.graph = 0;
+    CHECK(!cut(40000, mean, NRM_F32, NRM_BF16) && g_args.header.rows_per_block == 2);
+    CHECK(!cut(40000, mean, NRM_BF16, NRM_BF16) && !cut(2000, mean, NRM_F32, NRM_F32));
+    c.bparams.graph = 1;
+  }
+  c.bparams.graph = 0;
+  CHECK(!cut(40000, 12287, NRM_F32, NRM_F32));
+  CHECK(cut(40000, 16385, NRM_BF16, NRM_BF16) && g_plan.res_grid == 768);
+}
+
 // Without resident rows a single-pass row of at most 2^RES_LOG2 elements is run by
 // its block in every batch (its bits must not depend on the other rows), and
 // batches of short rows are cut up as they are with resident rows.
@@ -326,6 +350,7 @@ int main(int argc, char** argv) {
       {"workspace_layout", test_workspace_layout},
       {"tree_height", test_tree_height},
       {"apart_rule", test_apart_rule},
+      {"cuts_of_one_segment_rows", test_cuts_of_one_segment_rows},
       {"cuts_of_wavefront_rows", test_cuts_of_wavefront_rows},
       {"cuts_without_resident_rows", test_cuts_without_resident_rows},
   };

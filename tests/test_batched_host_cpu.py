@@ -27,7 +27,8 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["rows_grid", "captured_tables", "failed_launch", "workspace_layout", "tree_height",
-                                  "apart_rule", "cuts_without_resident_rows", "cuts_of_wavefront_rows"])
+                                  "apart_rule", "cuts_without_resident_rows", "cuts_of_wavefront_rows",
+                                  "cuts_of_one_segment_rows"])
 def test_batched_host(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
