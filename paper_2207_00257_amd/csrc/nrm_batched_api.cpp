@@ -367,7 +367,8 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 // blocks 2 at a time 590; 12000 of 32 to 2^18 482, 493 and 537; 7895 x 17000 230,
 // 235 and 276). In large batches of binary32 in and out the same pays from three
 // quarters of that mean on (16384 rows of 32 to 2^17: 372 us listed, 404 us run;
-// 39431 x 13074 647 and 755), not in small ones (2000 x 12000: 50 and 38) nor where
+// 39431 x 13074 647 and 755), from 2^27 elements on from two thirds (36363 x 11000
+// 545 and 569; 6100 x 11000 103 and 97), not in small ones (2000 x 12000: 50 and 38) nor where
 // a segment is fewer bytes (10000 x 13074 to bfloat16: 165 and 138; 13421 x 10000
 // bfloat16: 191 and 103).
 // Below that it depends on how the lengths spread, which the host does not know
@@ -379,14 +380,16 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 void cut_rows(const nrm_batch_params& p, int64_t rows, int64_t elems, BatchHeader* h) {
   const int64_t mean = elems / rows;
   const int64_t block_max = int64_t(1) << nrm::RES_LOG2;
-  const bool large_f32 = h->mode == nrm::BATCH_CSR && h->csr_in_dt == NRM_F32 && h->csr_out_dt == NRM_F32 &&
-                         elems >= (int64_t(1) << 26);
+  const bool f32 = h->mode == nrm::BATCH_CSR && h->csr_in_dt == NRM_F32 && h->csr_out_dt == NRM_F32;
+  const int64_t listed_mean = f32 && elems >= (int64_t(1) << 27)   ? block_max / 3 * 2
+                              : f32 && elems >= (int64_t(1) << 26) ? block_max / 4 * 3
+                                                                   : block_max + 1;
   const int64_t wave_mean = h->mode == nrm::BATCH_CSR && nrm::dtype_size(h->csr_in_dt) == 2 ? nrm::WAVE_MAX_ELEMS
                                                                                         : nrm::WAVE_MAX_ELEMS / 8 * 7;
   h->run_max = std::min(block_max, short_max_of(p));
   if (rows <= 512) {
     h->rows_per_block = 1;
-  } else if (mean > block_max || (large_f32 && mean >= block_max / 4 * 3)) {
+  } else if (mean >= listed_mean) {
     h->rows_per_block = rows <= 4096 ? nrm::ROWS_WAVES : nrm::ROWS_MAX;
     if (p.resident_segments > 0) h->run_max = 0;
   } else {

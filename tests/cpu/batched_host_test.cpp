@@ -272,7 +272,8 @@ static void test_cuts_of_one_segment_rows() {
     c.bparams.graph = 1;
   }
   c.bparams.graph = 0;
-  CHECK(!cut(40000, 12287, NRM_F32, NRM_F32));
+  CHECK(cut(40000, 10922, NRM_F32, NRM_F32) && !cut(40000, 10921, NRM_F32, NRM_F32));  // 2^27 elements and more
+  CHECK(cut(6000, 12288, NRM_F32, NRM_F32) && !cut(6000, 12287, NRM_F32, NRM_F32));    // 2^26 and more
   CHECK(cut(40000, 16385, NRM_BF16, NRM_BF16) && g_plan.res_grid == 768);
 }
 
