@@ -131,7 +131,8 @@ typedef struct {
  * block, unroll, map_unroll, grid, short_regs, map_block and map_grid shape the
  * three launches that take the longer rows when resident_segments is 0; with
  * resident rows those rows are units of one persistent kernel, or in a large batch
- * mostly of them three launches, of which the map_ parameters shape the divide. */
+ * mostly of them three launches, of which the map_ parameters shape the divide
+ * (map_grid at least 2048 there, in larger batches 4096, softmax 8192). */
 typedef struct {
   int32_t block;       /* threads per block: 64..1024, multiple of 64 */
   int32_t unroll;      /* tile sums: 16-byte vectors per thread per iteration: 1, 2, 4, 8 */

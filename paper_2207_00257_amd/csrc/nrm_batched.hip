@@ -649,8 +649,8 @@ __global__ void __launch_bounds__(RES_BLOCK) __attribute__((amdgpu_waves_per_eu(
 // HBM bounds it, three transfers. The persistent kernel takes the tiles from a
 // counter, which serves one per 14 to 17 ns, holds 80 registers for the segments,
 // and waits for each unit's row total: 16 rows of 20,000,000 binary32 676 us there,
-// 611 us here (5.8 TB/s over 3.84 GB less what the cache keeps), bfloat16 424 and
-// 318 us. Small batches lose here to the launches' starts, and those with wider
+// 603 us here (6.4 TB/s over 3.84 GB, less what the cache keeps), bfloat16 424 and
+// 313 us. Small batches lose here to the launches' starts, and those with wider
 // outputs than inputs to phase 2's two stores per vector: see the host's rule.
 
 template <int ACC>

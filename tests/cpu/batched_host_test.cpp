@@ -319,7 +319,11 @@ static void test_apart_rule() {
   CHECK(!apart(64, b, NRM_F32, NRM_F32));  // mean 2^20
   CHECK(apart(1, b, NRM_F32, NRM_BF16) && !apart(1, b, NRM_BF16, NRM_F32) && !apart(1, w - 1, NRM_F16, NRM_F32));
   CHECK(apart(1, w, NRM_BF16, NRM_F32));
-  CHECK(apart(511, w, NRM_F32, NRM_F32) && !apart(512, w, NRM_F32, NRM_F32));  // mean 2^18
+  CHECK(apart(511, w, NRM_F32, NRM_F32) && g_plan.map_grid == 2048 && !apart(512, w, NRM_F32, NRM_F32));  // mean 2^18
+  CHECK(apart(1, 2 * w, NRM_F32, NRM_F32) && g_plan.map_grid == 4096);
+  c.bparams.map_grid = 10000;
+  CHECK(apart(1, 2 * w, NRM_F32, NRM_F32) && g_plan.map_grid == 10000);
+  c.bparams.map_grid = 1024;
   c.bparams.resident_segments = 0;
   CHECK(!apart(1, w, NRM_F32, NRM_F32));
   c.bparams.resident_segments = 64;
