@@ -379,7 +379,9 @@ hipError_t set_rows_node(const nrm::BatchGraph& g, const BatchPlan& p, BatchArgs
 // 39431 x 13074 647 and 755), from 2^27 elements on from two thirds (36363 x 11000
 // 545 and 569; 6100 x 11000 103 and 97), not in small ones (2000 x 12000: 50 and 38) nor where
 // a segment is fewer bytes (10000 x 13074 to bfloat16: 165 and 138; 13421 x 10000
-// bfloat16: 191 and 103).
+// bfloat16: 191 and 103). Above 2^14 2-byte rows gain like the others if they are
+// alike (16384 x 20000 bfloat16 443 us listed, 533 run), and lose if most are below
+// it (14532 rows of 1320 to 71892 float16, mean 17806: 323 and 299).
 // Below that it depends on how the lengths spread, which the host does not know
 // (32768 rows of 32 to 2^16, mean 8600: 398 listed, 447 run; 16384 x 8192: 239 and
 // 194).
